@@ -5,17 +5,16 @@
 //   dW          : dW[d_c, H*(d_nope+d_v)] = c_kv^T @ dKV  (split over tokens,
 //                 fixed-order reduction: deterministic)
 //
-// One kernel template covers all three: each operand is either "k-contiguous"
-// (stored [rows][K]) or "k-strided" (stored [K][rows]); both are staged into
-// LDS as stored and strided operands are read back with transposing LDS reads,
-// so there is no transpose pass anywhere. The output tile is computed as
-// C^T = B^T A^T block by block, which puts 4 consecutive output columns in each
-// lane's accumulators for vectorised stores.
+// Each operand is either "k-contiguous" (stored [rows][K]) or "k-strided" (stored
+// [K][rows]); both are staged into LDS as stored and strided operands are read back with
+// transposing LDS reads, so there is no transpose pass anywhere. The output tile is
+// computed as C^T = B^T A^T block by block, which puts 4 consecutive output columns in
+// each lane's accumulators for vectorised stores.
 //
-// The reconstruct (a 512-long contraction writing 256 bytes per output row and head)
-// runs as a persistent variant of the large-tile kernel that spreads each tile's
-// stores over the next tile's MFMAs (gemm_stream_kernel); dc and dW, whose dKV operand
-// comes as a bf16 pair hi + lo, run the large tiles on eight waves (gemm_big8_kernel).
+// bf16: gemm_ring_kernel, an LDS ring of direct copies at three tile sizes, for any number
+// of tokens; the reconstruct (a 512-long contraction writing 256 bytes per output row and
+// head) runs large problems on a persistent variant that spreads each tile's stores over
+// the next tile's MFMAs (gemm_stream_kernel). fp32: the register-staged gemm_kernel.
 //
 // Per output element the contraction runs over K in ascending 16-wide steps
 // (one MFMA each) with fp32 accumulation; tile shapes and the dW token split do
@@ -25,6 +24,8 @@
 // direct global->LDS copies issued as inline assembly (exact LDS-read waits; the
 // ring orders the copies with explicit waits and barriers)
 #define LAGA_LDS_DMA_ASM 1
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -33,6 +34,14 @@ namespace laga {
 namespace {
 
 constexpr int kThreads = 256;
+
+// xcd_remap for any n: the first n % 8 XCDs receive one id more. Partial row tiles give tile
+// counts that are no multiple of 8, and workgroups that share operands then have to meet in
+// one L2 all the same (dc, 10002 tokens, 128 x 128 tiles: 239 us without, 112 us with it).
+__device__ __forceinline__ int xcd_remap_any(int id, int n) {
+  const int x = id % 8;
+  return x * (n / 8) + min(x, n % 8) + id / 8;
+}
 
 template <typename T, bool KSTRIDED, int ROWS, int BK>
 struct OperandTile {
@@ -97,22 +106,15 @@ __device__ __forceinline__ void store4<bf16>(bf16* p, float a, float b, float c,
 }
 
 // C (+ blockIdx.z * split_stride) [M][N] = A[M][K-range] B[K-range][N]
-// SPLIT = 1: A is the sum of two arrays A + A2 of the same layout; SPLIT = 2: B = B + B2.
-// (A value held as a bf16 pair hi + lo keeps ~16 significant bits through a bf16 MFMA;
-// per k-step the hi product is accumulated before the lo product.)
-template <typename T, typename TO, bool A_KS, bool B_KS, int BM, int BN, int BK, int SPLIT>
+template <typename T, typename TO, bool A_KS, bool B_KS, int BM, int BN, int BK>
 __global__ __launch_bounds__(kThreads) void gemm_kernel(
-    const T* __restrict__ A, const T* __restrict__ B, const T* __restrict__ X2, TO* __restrict__ C,
+    const T* __restrict__ A, const T* __restrict__ B, TO* __restrict__ C,
     int M, int N, int K, int lda, int ldb, int ldc, int k_chunk, long long split_stride) {
   using TA = OperandTile<T, A_KS, BM, BK>;
   using TB = OperandTile<T, B_KS, BN, BK>;
   constexpr int WM = BM / 64, WN = BN / 64;  // 32x32 blocks per wave along m and n
-  constexpr int A2_ELEMS = SPLIT == 1 ? TA::LDS_ELEMS : 1;
-  constexpr int B2_ELEMS = SPLIT == 2 ? TB::LDS_ELEMS : 1;
   __shared__ __attribute__((aligned(16))) T sA[TA::LDS_ELEMS];
   __shared__ __attribute__((aligned(16))) T sB[TB::LDS_ELEMS];
-  __shared__ __attribute__((aligned(16))) T sA2[A2_ELEMS];
-  __shared__ __attribute__((aligned(16))) T sB2[B2_ELEMS];
 
   const int n_tiles = (N + BN - 1) / BN;
   const int m_tiles = (M + BM - 1) / BM;
@@ -133,17 +135,13 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.f;
 
-  TA ta, ta2; TB tb, tb2;
+  TA ta; TB tb;
   auto load = [&](int k0) {
     ta.load(A, lda, m0, M, k0, ke);
     tb.load(B, ldb, n0, N, k0, ke);
-    if (SPLIT == 1) ta2.load(X2, lda, m0, M, k0, ke);
-    if (SPLIT == 2) tb2.load(X2, ldb, n0, N, k0, ke);
   };
   auto store = [&]() {
     ta.store(sA); tb.store(sB);
-    if (SPLIT == 1) ta2.store(sA2);
-    if (SPLIT == 2) tb2.store(sB2);
   };
   load(kb);
   store();
@@ -158,37 +156,10 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(
       for (int i = 0; i < WM; ++i) fa[i] = TA::frag(sA, (wm * WM + i) * 32, ks);
 #pragma unroll
       for (int j = 0; j < WN; ++j) fb[j] = TB::frag(sB, (wn * WN + j) * 32, ks);
-      if (SPLIT == 0) {
 #pragma unroll
-        for (int j = 0; j < WN; ++j)
+      for (int j = 0; j < WN; ++j)
 #pragma unroll
-          for (int i = 0; i < WM; ++i) mma(acc[j][i], fb[j], fa[i]);
-      } else if (SPLIT == 1) {
-        frag_t<T> fa2[WM];
-#pragma unroll
-        for (int i = 0; i < WM; ++i) fa2[i] = TA::frag(sA2, (wm * WM + i) * 32, ks);
-        // all hi products, then all lo ones (per accumulator the same order; see gemm_big_kernel)
-#pragma unroll
-        for (int j = 0; j < WN; ++j)
-#pragma unroll
-          for (int i = 0; i < WM; ++i) mma(acc[j][i], fb[j], fa[i]);
-#pragma unroll
-        for (int j = 0; j < WN; ++j)
-#pragma unroll
-          for (int i = 0; i < WM; ++i) mma(acc[j][i], fb[j], fa2[i]);
-      } else {
-        frag_t<T> fb2[WN];
-#pragma unroll
-        for (int j = 0; j < WN; ++j) fb2[j] = TB::frag(sB2, (wn * WN + j) * 32, ks);
-#pragma unroll
-        for (int j = 0; j < WN; ++j)
-#pragma unroll
-          for (int i = 0; i < WM; ++i) mma(acc[j][i], fb[j], fa[i]);
-#pragma unroll
-        for (int j = 0; j < WN; ++j)
-#pragma unroll
-          for (int i = 0; i < WM; ++i) mma(acc[j][i], fb2[j], fa[i]);
-      }
+        for (int i = 0; i < WM; ++i) mma(acc[j][i], fb[j], fa[i]);
     }
     __syncthreads();
     if (more) { store(); __syncthreads(); }
@@ -211,18 +182,18 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(
     }
 }
 
-// ------------------------------------------------------------------ large tiles (bf16)
-// A workgroup of four waves computes a BM x BN output tile (BM * BN = 4 * 128 * 128),
-// one wave per SIMD, each wave 128 x 128 (4 x 4 blocks of 32 x 32, 256 accumulator
-// registers per lane): an LDS operand fragment then feeds four MFMAs, so LDS reads
-// stay well under the LDS rate. Besides 256 x 256, 128 x 512 and 512 x 128 tiles cover
-// a whole 512-wide side, so the other (large) operand is read from memory once (the
-// backward's dc and dW take those shapes on gemm_big8_kernel below, two waves per SIMD).
-// The contraction advances 32 at a time through an LDS ring of NSLOT stages filled by
-// direct global->LDS copies issued NSLOT - 1 stages ahead (a stage of MFMAs is shorter
-// than the latency of a load from memory); one barrier per stage, placed inside the
-// second half of the stage's MFMAs, with the next stage's first operands read before
-// the last MFMAs.
+// ------------------------------------------------------------------ ring tiles (bf16)
+// A workgroup computes a BM x BN output tile on two waves per SIMD (eight waves, or four
+// and two workgroups per CU), so that one wave's copies, LDS reads and barrier waits run
+// beside the other's MFMAs: each wave owns 64 x 128, 128 x 64 (8 accumulator blocks of
+// 32 x 32) or 64 x 64 (4 blocks) of it. The 256 x 256, 128 x 512 and 512 x 128 tiles read
+// the least per product (the last two cover a whole 512-wide side, so the other, large
+// operand is read from memory once); 256 x 128 and 128 x 128 are for problems with too few
+// of those (launch_ring has the rule). The contraction advances 32 at a time through an LDS
+// ring of NSLOT stages filled by direct global->LDS copies issued NSLOT - 1 stages ahead
+// (a stage of MFMAs is shorter than the latency of a load from memory); one barrier per
+// stage, between its two 16-wide steps, with the next stage's first operands read before
+// the last MFMAs. Refills and waits are branch-free until the last NSLOT stages.
 //
 // Operand tiles are ROWS (the non-contraction index) x 32 contraction indices, stored
 // unpadded as the copies fill them (a wave instruction fills 64 consecutive 16-byte
@@ -262,6 +233,35 @@ struct GFill {
 #pragma unroll
     for (int i = 0; i < PER; ++i) g2lds16_so(stage_origin, off[i], tile + (wave + NWV * i) * 512);
   }
+  // a k-contiguous tile of which only the first `rows` rows exist (init with r0 = 0 and no
+  // limit): the others copy row rows - 1
+  __device__ __forceinline__ void fill_rows(const bf16* stage_origin, bf16* tile, int wave, int l, int ld,
+                                            int rows) const {
+    static_assert(!KS, "rows of a k-contiguous operand");
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int over = max((((wave + NWV * i) * 64 + l) >> 2) - (rows - 1), 0);
+      g2lds16_so(stage_origin, off[i] - 2u * (uint32_t)(over * ld), tile + (wave + NWV * i) * 512);
+    }
+  }
+  // a stage of which only the first `tail` contraction indices exist (a multiple of 8 for
+  // k-contiguous tiles): the chunks of the others copy the stage's index 0 instead
+  __device__ __forceinline__ void fill_part(const bf16* stage_origin, bf16* tile, int wave, int l, int ld,
+                                            int tail) const {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int p = (wave + NWV * i) * 64 + l;
+      uint32_t o = off[i];
+      if (!KS) {
+        const int c = (p & 3) ^ (((p >> 2) >> 2) & 3);
+        if (c * 8 >= tail) o -= 2u * (uint32_t)(c * 8);
+      } else {
+        const int kr = p / CPR;
+        if (kr >= tail) o -= 2u * (uint32_t)(kr * ld);
+      }
+      g2lds16_so(stage_origin, o, tile + (wave + NWV * i) * 512);
+    }
+  }
 };
 
 // Operand fragments of one wave's BW 32-row blocks (rows 32 BW wsel .. of the tile),
@@ -296,191 +296,37 @@ struct GRead {
 };
 
 // C (+ blockIdx.z * split_stride) [M][N] = A[M][k range] B[k range][N], bf16 operands,
-// fp32 accumulation. SPLIT as in gemm_kernel (1: A + X2, 2: B + X2; hi before lo per
-// k-step). The k range of a split is a multiple of 32; M, N multiples of 8.
-template <int BM, int BN, bool A_KS, bool B_KS, int SPLIT, typename TO>
-__global__ __launch_bounds__(256, 1) void gemm_big_kernel(
+// fp32 accumulation, on NWV waves in a WGM x (NWV / WGM) grid of wave tiles. SPLIT as in
+// gemm_kernel (1: A + X2, 2: B + X2; hi before lo per k-step). M and N are arbitrary for
+// k-contiguous operands and at least 8 for k-strided ones (rows or columns past the end
+// are copied from the last ones and not stored). The contraction of a split may end
+// anywhere if both operands are k-strided, else at a multiple of 16: the last stage then
+// copies in-bounds rows (k-strided) or chunks (k-contiguous) in the place of the missing
+// ones, k-strided rows past the end are zeroed in LDS before they are read, and a second
+// 16-wide step with nothing in it is left out.
+template <int BM, int BN, int NWV, int WGM, int NSLOT, bool A_KS, bool B_KS, int SPLIT, typename TO>
+__global__ __launch_bounds__(64 * NWV, NWV == 4 ? 2 : 1) void gemm_ring_kernel(
     const bf16* __restrict__ A, const bf16* __restrict__ B, const bf16* __restrict__ X2, TO* __restrict__ C,
     int M, int N, int K, int lda, int ldb, int ldc, int k_chunk, long long split_stride) {
-  static_assert(BM * BN == 4 * 128 * 128 && BM % 128 == 0 && BN % 128 == 0, "four 128 x 128 waves");
-  constexpr int WM = BM / 128;                     // waves along m
-  constexpr int NT = SPLIT ? 3 : 2;                // operand tiles per stage: A, B (, X2)
-  constexpr int NSLOT = SPLIT ? 3 : 4;             // ring depth (LDS: 144 or 128 KB)
-  constexpr bool X_KS = SPLIT == 1 ? A_KS : B_KS;
-  constexpr int XR = SPLIT == 1 ? BM : BN;         // rows of the X2 tile
-  constexpr int TA = BM * kGK, TB = BN * kGK, TX = SPLIT ? XR * kGK : 0;
-  constexpr int STAGE = TA + TB + TX;              // elements per stage
-  __shared__ __attribute__((aligned(16))) bf16 sm[NSLOT * STAGE];
-
-  const int n_tiles = (N + BN - 1) / BN, m_tiles = (M + BM - 1) / BM;
-  const int lin = xcd_remap(blockIdx.x, n_tiles * m_tiles);
-  const int tn = lin % n_tiles, tm = lin / n_tiles;
-  const int m0 = tm * BM, n0 = tn * BN;
-  const int kb = blockIdx.z * k_chunk;
-  const int nst = (min(K, kb + k_chunk) - kb) / kGK;  // stages
-
-  const int l = threadIdx.x & 63, g = l >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3;
-  const int wm = wave % WM, wn = wave / WM;
-
-  GFill<A_KS, BM> fa;
-  GFill<B_KS, BN> fb;
-  GFill<X_KS, XR> fx;
-  fa.init(wave, l, lda, m0, M);
-  fb.init(wave, l, ldb, n0, N);
-  if (SPLIT) fx.init(wave, l, SPLIT == 1 ? lda : ldb, SPLIT == 1 ? m0 : n0, SPLIT == 1 ? M : N);
-  auto fill = [&](int slot, int k) {
-    bf16* st = sm + slot * STAGE;
-    fa.fill(A_KS ? A + (size_t)k * lda : A + k, st, wave);
-    fb.fill(B_KS ? B + (size_t)k * ldb : B + k, st + TA, wave);
-    if (SPLIT == 1) fx.fill(A_KS ? X2 + (size_t)k * lda : X2 + k, st + TA + TB, wave);
-    if (SPLIT == 2) fx.fill(B_KS ? X2 + (size_t)k * ldb : X2 + k, st + TA + TB, wave);
-  };
-  constexpr int F = GFill<A_KS, BM>::PER + GFill<B_KS, BN>::PER + (SPLIT ? GFill<X_KS, XR>::PER : 0);
-  // wait until the copies of a stage have landed while `ahead` later stages may still
-  // be in flight (copies complete in issue order)
-  auto wait_stage = [](int ahead) {
-    if (ahead >= 3) wait_vmem_le<3 * F>();
-    else if (ahead == 2) wait_vmem_le<2 * F>();
-    else if (ahead == 1) wait_vmem_le<F>();
-    else wait_vmem();
-  };
-  static_assert(NSLOT <= 4 && 3 * F < 64, "vmcnt range");
-
-  GRead<A_KS, BM> ra;
-  GRead<B_KS, BN> rb;
-  GRead<X_KS, XR> rx;
-  ra.init(l, wm);
-  rb.init(l, wn);
-  const int xsel = SPLIT == 1 ? wm : wn;
-  if (SPLIT) rx.init(l, xsel);
-
-  f32x16 acc[4][4];  // [n block][m block]: C^T blocks, lane <-> m, 4 consecutive n per lane
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[j][i] = f32x16{};
-
-  bf16x8 fA[2][4], fB[2][4], fX[2][4];  // operands of contraction steps 0 and 1 of a stage
-  auto read = [&](int slot, int ks) {
-    const bf16* st = sm + slot * STAGE;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      fA[ks][j] = ra.get(st, wm, ks, j);
-      fB[ks][j] = rb.get(st + TA, wn, ks, j);
-      if (SPLIT) fX[ks][j] = rx.get(st + TA + TB, xsel, ks, j);
-    }
-  };
-  // n blocks [j0, j1) of step ks. With a low-half operand every accumulator takes the hi
-  // product before the lo one as before, but all hi products of the call are issued first:
-  // an MFMA that accumulates onto the one just issued waits for its result, so back-to-back
-  // hi, lo pairs on one accumulator would run the matrix unit at half rate.
-  auto mmas = [&](int ks, int j0, int j1) {
-#pragma unroll
-    for (int j = j0; j < j1; ++j)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) mma(acc[j][i], fB[ks][j], fA[ks][i]);
-    if (SPLIT)
-#pragma unroll
-      for (int j = j0; j < j1; ++j)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          if (SPLIT == 1) mma(acc[j][i], fB[ks][j], fX[ks][i]);
-          if (SPLIT == 2) mma(acc[j][i], fX[ks][j], fA[ks][i]);
-        }
-  };
-
-  const int npre = min(NSLOT, nst);
-  for (int t = 0; t < npre; ++t) fill(t, kb + t * kGK);
-  wait_stage(npre - 1);  // stage 0 has landed
-  lds_barrier();
-  read(0, 0);
-  // (the last stage is peeled: every trip of the loop then ends with the next stage's
-  // first operands in flight, and the compiler's LDS waits stay exact)
-  // Instruction order within a stage (the scheduler would otherwise bunch the LDS
-  // reads and the waits on them): step-1 reads interleaved with the step-0 MFMAs, in
-  // four groups; then half of the step-1 MFMAs; barrier and copies; the next stage's
-  // step-0 reads interleaved with the other half.
-  constexpr int RPS = (A_KS ? 8 : 4) + (B_KS ? 8 : 4) + (SPLIT ? (X_KS ? 8 : 4) : 0);  // LDS reads per step
-  constexpr int MPJ = SPLIT ? 8 : 4;  // MFMAs per n block and step
-  constexpr int DS_READ = 0x100, MFMA = 0x008;
-  for (int t = 0; t < nst - 1; ++t) {
-    const int slot = t % NSLOT;
-    read(slot, 1);
-    mmas(0, 0, 4);
-    mmas(1, 0, 2);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      __builtin_amdgcn_sched_group_barrier(DS_READ, RPS / 4, 0);
-      __builtin_amdgcn_sched_group_barrier(MFMA, MPJ, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(MFMA, 2 * MPJ, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    wait_stage(min(NSLOT - 2, nst - 2 - t));  // this wave's copies of stage t + 1 have landed
-    lds_barrier();  // ... everyone's; and every read of stage t is done
-    if (t + NSLOT < nst) fill(slot, kb + (t + NSLOT) * kGK);
-    __builtin_amdgcn_sched_barrier(0);
-    read((t + 1) % NSLOT, 0);
-    mmas(1, 2, 4);
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      __builtin_amdgcn_sched_group_barrier(DS_READ, RPS / 2, 0);
-      __builtin_amdgcn_sched_group_barrier(MFMA, MPJ, 0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  read((nst - 1) % NSLOT, 1);
-  mmas(0, 0, 4);
-  mmas(1, 0, 4);
-
-  TO* Cz = C + blockIdx.z * split_stride;
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int m = m0 + 128 * wm + 32 * i + (l & 31);
-      if (m >= M) continue;
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        const int n = n0 + 128 * wn + 32 * j + rr * 8 + g * 4;
-        if (n < N)
-          store4<TO>(Cz + (size_t)m * ldc + n, acc[j][i][4 * rr], acc[j][i][4 * rr + 1], acc[j][i][4 * rr + 2],
-                     acc[j][i][4 * rr + 3]);
-      }
-    }
-}
-
-// The same product on eight waves, two per SIMD (the backward's dc and dW, whose dKV
-// operand is a bf16 pair hi + lo, and W_o's backward): each wave owns 64 x 128
-// (BM <= BN) or 128 x 64 of the output, 8 accumulator blocks (128 registers), so two
-// waves fit on a SIMD and one wave's copies, LDS reads and barrier waits overlap the
-// other's MFMAs. Stages, copies, swizzles and the per-element accumulation order
-// (ascending 16-wide steps, hi before lo per step) are gemm_big_kernel's, so results
-// are bit-identical to it.
-template <int BM, int BN, bool A_KS, bool B_KS, int SPLIT, typename TO>
-__global__ __launch_bounds__(512, 1) void gemm_big8_kernel(
-    const bf16* __restrict__ A, const bf16* __restrict__ B, const bf16* __restrict__ X2, TO* __restrict__ C,
-    int M, int N, int K, int lda, int ldb, int ldc, int k_chunk, long long split_stride) {
-  static_assert(BM * BN == 4 * 128 * 128, "the 4-wave tile shapes");
-  constexpr int NWV = 8;
-  constexpr int WGM = BM <= BN ? 2 : 4, WGN = NWV / WGM;  // waves along m, along n
-  constexpr int WTM = BM / WGM, WTN = BN / WGN;           // one wave's output tile
-  constexpr int NI = WTM / 32, NJ = WTN / 32;             // its 32 x 32 blocks
-  static_assert(NI * NJ == 8 && (NI == 2 || NI == 4) && (NJ == 2 || NJ == 4), "8 blocks per wave");
-  constexpr int NSLOT = SPLIT ? 3 : 4;                    // ring depth (144 or 128 KB)
+  constexpr int WGN = NWV / WGM;                 // waves along n (WGM along m)
+  constexpr int WTM = BM / WGM, WTN = BN / WGN;  // one wave's output tile
+  constexpr int NI = WTM / 32, NJ = WTN / 32;    // its 32 x 32 blocks
+  static_assert((NI == 2 || NI == 4) && (NJ == 2 || NJ == 4), "two or four blocks per wave and side");
   constexpr bool X_KS = SPLIT == 1 ? A_KS : B_KS;
   constexpr int XR = SPLIT == 1 ? BM : BN;
-  constexpr int XB = SPLIT == 1 ? NI : NJ;                // X2 blocks per wave
+  constexpr int XB = SPLIT == 1 ? NI : NJ;       // X2 blocks per wave
   constexpr int TA = BM * kGK, TB = BN * kGK, TX = SPLIT ? XR * kGK : 0;
   constexpr int STAGE = TA + TB + TX;
   __shared__ __attribute__((aligned(16))) bf16 sm[NSLOT * STAGE];
 
   const int n_tiles = (N + BN - 1) / BN, m_tiles = (M + BM - 1) / BM;
-  const int lin = xcd_remap(blockIdx.x, n_tiles * m_tiles);
+  const int lin = xcd_remap_any(blockIdx.x, n_tiles * m_tiles);
   const int tn = lin % n_tiles, tm = lin / n_tiles;
   const int m0 = tm * BM, n0 = tn * BN;
   const int kb = blockIdx.z * k_chunk;
-  const int nst = (min(K, kb + k_chunk) - kb) / kGK;
+  const int klen = min(K, kb + k_chunk) - kb;
+  const int nst = (klen + kGK - 1) / kGK;
+  const int tail = klen - (nst - 1) * kGK;  // contraction indices of the last stage, 1 .. 32
 
   const int l = threadIdx.x & 63, g = l >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & (NWV - 1);
@@ -492,12 +338,40 @@ __global__ __launch_bounds__(512, 1) void gemm_big8_kernel(
   fa.init(wave, l, lda, m0, M);
   fb.init(wave, l, ldb, n0, N);
   if (SPLIT) fx.init(wave, l, SPLIT == 1 ? lda : ldb, SPLIT == 1 ? m0 : n0, SPLIT == 1 ? M : N);
-  auto fill = [&](int slot, int k) {
-    bf16* st = sm + slot * STAGE;
+  auto fill = [&](int t) {
+    const int k = kb + t * kGK;
+    bf16* st = sm + (t % NSLOT) * STAGE;
     fa.fill(A_KS ? A + (size_t)k * lda : A + k, st, wave);
     fb.fill(B_KS ? B + (size_t)k * ldb : B + k, st + TA, wave);
     if (SPLIT == 1) fx.fill(A_KS ? X2 + (size_t)k * lda : X2 + k, st + TA + TB, wave);
     if (SPLIT == 2) fx.fill(B_KS ? X2 + (size_t)k * ldb : X2 + k, st + TA + TB, wave);
+  };
+  auto fill_last = [&]() {  // stage nst - 1
+    if (tail == kGK) return fill(nst - 1);
+    const int k = kb + (nst - 1) * kGK;
+    bf16* st = sm + ((nst - 1) % NSLOT) * STAGE;
+    fa.fill_part(A_KS ? A + (size_t)k * lda : A + k, st, wave, l, lda, tail);
+    fb.fill_part(B_KS ? B + (size_t)k * ldb : B + k, st + TA, wave, l, ldb, tail);
+    if (SPLIT == 1) fx.fill_part(A_KS ? X2 + (size_t)k * lda : X2 + k, st + TA + TB, wave, l, lda, tail);
+    if (SPLIT == 2) fx.fill_part(B_KS ? X2 + (size_t)k * ldb : X2 + k, st + TA + TB, wave, l, ldb, tail);
+  };
+  // after the copies of the last stage have landed in every wave: zeros for its k-strided
+  // rows past the end of the contraction (both operands: no product of a missing index
+  // meets a value of another one)
+  auto zero_last = [&]() {
+    if constexpr (A_KS && B_KS) {
+      if (tail % 16 == 0) return;
+      const int r1 = tail > 16 ? 32 : 16;
+      bf16* st = sm + ((nst - 1) % NSLOT) * STAGE;
+      auto zero = [&](bf16* tile, int rows) {
+        for (int c = tail * (rows / 8) + (int)threadIdx.x; c < r1 * (rows / 8); c += 64 * NWV)
+          *reinterpret_cast<chunk16*>(tile + c * 8) = zero_chunk();
+      };
+      zero(st, BM);
+      zero(st + TA, BN);
+      if (SPLIT) zero(st + TA + TB, XR);
+      lds_barrier();
+    }
   };
   constexpr int F = GFill<A_KS, BM, NWV>::PER + GFill<B_KS, BN, NWV>::PER + (SPLIT ? GFill<X_KS, XR, NWV>::PER : 0);
   auto wait_stage = [](int ahead) {
@@ -506,7 +380,7 @@ __global__ __launch_bounds__(512, 1) void gemm_big8_kernel(
     else if (ahead == 1) wait_vmem_le<F>();
     else wait_vmem();
   };
-  static_assert(3 * F < 64, "vmcnt range");
+  static_assert(NSLOT <= 4 && 3 * F < 64, "vmcnt range");
 
   GRead<A_KS, BM, NI> ra;
   GRead<B_KS, BN, NJ> rb;
@@ -523,8 +397,8 @@ __global__ __launch_bounds__(512, 1) void gemm_big8_kernel(
     for (int i = 0; i < NI; ++i) acc[j][i] = f32x16{};
 
   bf16x8 fA[2][NI], fB[2][NJ], fX[2][XB];
-  auto read = [&](int slot, int ks) {
-    const bf16* st = sm + slot * STAGE;
+  auto read = [&](int t, int ks) {
+    const bf16* st = sm + (t % NSLOT) * STAGE;
 #pragma unroll
     for (int i = 0; i < NI; ++i) fA[ks][i] = ra.get(st, wm, ks, i);
 #pragma unroll
@@ -533,7 +407,8 @@ __global__ __launch_bounds__(512, 1) void gemm_big8_kernel(
 #pragma unroll
       for (int x = 0; x < XB; ++x) fX[ks][x] = rx.get(st + TA + TB, xsel, ks, x);
   };
-  // every hi product of the step, then every lo one (per accumulator: hi before lo)
+  // every hi product of the step, then every lo one (per accumulator: hi before lo; an
+  // MFMA that accumulates onto the one just issued would wait for its result)
   auto mmas = [&](int ks) {
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
@@ -550,23 +425,36 @@ __global__ __launch_bounds__(512, 1) void gemm_big8_kernel(
   };
 
   const int npre = min(NSLOT, nst);
-  for (int t = 0; t < npre; ++t) fill(t, kb + t * kGK);
+  for (int t = 0; t < npre; ++t) {
+    if (t < nst - 1) fill(t);
+    else fill_last();
+  }
   wait_stage(npre - 1);
   lds_barrier();
+  if (nst == 1) zero_last();
   read(0, 0);
-  for (int t = 0; t < nst - 1; ++t) {
-    const int slot = t % NSLOT;
-    read(slot, 1);
+  // refill: 0 a whole stage, 1 the last stage, 2 none left
+  auto step = [&](int t, auto refill) {
+    constexpr int R = decltype(refill)::value;
+    read(t, 1);
     mmas(0);
-    wait_stage(min(NSLOT - 2, nst - 2 - t));  // this wave's copies of stage t + 1 have landed
-    lds_barrier();                            // ... everyone's; every read of stage t is done
-    if (t + NSLOT < nst) fill(slot, kb + (t + NSLOT) * kGK);
-    read((t + 1) % NSLOT, 0);
+    if constexpr (R < 2) wait_vmem_le<(NSLOT - 2) * F>();
+    else wait_stage(nst - 2 - t);  // this wave's copies of stage t + 1 have landed
+    lds_barrier();                 // ... everyone's; every read of stage t is done
+    if constexpr (R == 0) fill(t + NSLOT);
+    if constexpr (R == 1) fill_last();
+    if constexpr (R == 2)
+      if (t == nst - 2) zero_last();
+    read(t + 1, 0);
     mmas(1);
-  }
-  read((nst - 1) % NSLOT, 1);
+  };
+  int t = 0;
+  for (; t + NSLOT < nst - 1; ++t) step(t, std::integral_constant<int, 0>{});
+  if (t + NSLOT == nst - 1) step(t++, std::integral_constant<int, 1>{});
+  for (; t < nst - 1; ++t) step(t, std::integral_constant<int, 2>{});
+  if (tail > 16) read(nst - 1, 1);
   mmas(0);
-  mmas(1);
+  if (tail > 16) mmas(1);
 
   TO* Cz = C + blockIdx.z * split_stride;
 #pragma unroll
@@ -597,27 +485,30 @@ __global__ __launch_bounds__(512, 1) void gemm_big8_kernel(
 // consecutive columns per lane) into 16 16-byte stores per wave, issued one per stage
 // over the 16 stages of the next tile, so the writes run at an even rate behind the
 // MFMAs. Per output element the products are accumulated in the same order as in
-// gemm_big_kernel: the results are bitwise equal.
+// gemm_ring_kernel: the results are bitwise equal.
 //
 // Stores and copies share the in-order vmcnt counter: the stores issued in the last
 // three stages are younger than the copies a stage waits for (those were issued three
 // stages back) and older than none of them, so the ring's wait allows exactly that
 // many more operations in flight.
 constexpr int kStreamStoreStages = 16;  // stages over which a tile's stores are spread
+constexpr int kStreamMaxK = 1024;       // longest contraction it is launched for
 
 
-template <int BM, int BN, bool A_KS, bool B_KS>
+// RAGGED: the last row tile is partial (a variant of its own: the row limits in the whole-tile
+// one cost it 8 % at 16384 rows).
+template <int BM, int BN, bool A_KS, bool B_KS, bool RAGGED>
 __global__ __launch_bounds__(512, 1) void gemm_stream_kernel(const bf16* __restrict__ A, const bf16* __restrict__ B,
                                                              bf16* __restrict__ C, int M, int N, int K, int lda,
                                                              int ldb, int ldc) {
-  static_assert(BM == 256 && BN == 256, "eight 128 x 64 waves");
+  static_assert(BM == 256 && BN == 256 && !A_KS, "eight 128 x 64 waves; rows of A clamped at M");
   constexpr int WM = 2;  // waves along m (128 rows each); four along n (64 columns each)
   constexpr int NSLOT = 4;
   constexpr int TA = BM * kGK, TB = BN * kGK, STAGE = TA + TB;
   __shared__ __attribute__((aligned(16))) bf16 sm[NSLOT * STAGE];
   typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
-  const int n_tiles = N / BN, n_items = n_tiles * (M / BM);
+  const int n_tiles = N / BN, n_items = n_tiles * (RAGGED ? (M + BM - 1) / BM : M / BM);
   const int G = gridDim.x, nst = K / kGK;                    // nst >= kStreamStoreStages
   const int mine = (n_items - 1 - (int)blockIdx.x) / G + 1;  // tiles of this workgroup
   const int total = mine * nst;                              // stages of this workgroup
@@ -631,7 +522,8 @@ __global__ __launch_bounds__(512, 1) void gemm_stream_kernel(const bf16* __restr
   fa.init(wave, l, lda, 0, BM);  // offsets within a tile; the tile origin goes into the base
   fb.init(wave, l, ldb, 0, BN);
   auto tile_at = [&](int it, int& m0, int& n0) {
-    const int lin = xcd_remap((int)blockIdx.x + it * G, n_items);
+    const int id = (int)blockIdx.x + it * G;
+    const int lin = RAGGED ? xcd_remap_any(id, n_items) : xcd_remap(id, n_items);
     n0 = (lin % n_tiles) * BN;
     m0 = (lin / n_tiles) * BM;
   };
@@ -640,7 +532,8 @@ __global__ __launch_bounds__(512, 1) void gemm_stream_kernel(const bf16* __restr
   auto fill_next = [&](int slot) {
     const int k = f_loc * kGK;
     bf16* st = sm + slot * STAGE;
-    fa.fill(A_KS ? A + (size_t)k * lda + f_m0 : A + (size_t)f_m0 * lda + k, st, wave);
+    if (!RAGGED || f_m0 + BM <= M) fa.fill(A + (size_t)f_m0 * lda + k, st, wave);
+    else fa.fill_rows(A + (size_t)f_m0 * lda + k, st, wave, l, lda, M - f_m0);
     fb.fill(B_KS ? B + (size_t)k * ldb + f_n0 : B + (size_t)f_n0 * ldb + k, st + TA, wave);
     if (++f_loc == nst) {
       f_loc = 0;
@@ -696,10 +589,13 @@ __global__ __launch_bounds__(512, 1) void gemm_stream_kernel(const bf16* __restr
       out[p] = u32x4{r[0], s[0], r[1], s[1]};
     }
   };
-  // half hh (columns 16 hh .. of the block) of block b: one 16-byte store per lane
+  // half hh (columns 16 hh .. of the block) of block b: one 16-byte store per lane. Rows past
+  // M were copied from row M - 1 and hold its results: they are stored there again (the same
+  // bytes), so that every wave issues every store and the waits can count them.
   auto store = [&](const u32x4 (&v)[2], int m0, int n0, int b, int hh) {
     const int j = b >> 2, i = b & 3;
-    bf16* row = C + (size_t)(m0 + 128 * wm + 32 * i + (l & 31)) * ldc + n0 + 64 * wn + 32 * j + 8 * g;
+    const int m = m0 + 128 * wm + 32 * i + (l & 31);
+    bf16* row = C + (size_t)(RAGGED ? min(m, M - 1) : m) * ldc + n0 + 64 * wn + 32 * j + 8 * g;
     *reinterpret_cast<u32x4*>(row + 16 * hh) = v[hh];
   };
 
@@ -794,19 +690,9 @@ __global__ __launch_bounds__(512, 1) void gemm_stream_kernel(const bf16* __restr
   wait_vmem();  // the surplus copies land before the workgroup's LDS is released
 }
 
-// The streamed kernel applies to whole tiles and at least kStreamStoreStages stages per tile.
-bool gemm_stream_ok(int M, int N, int K, size_t a_elems, size_t b_elems) {
-  return M % 256 == 0 && N % 256 == 0 && K % kGK == 0 && K / kGK >= kStreamStoreStages && 2 * a_elems < (1ull << 32) &&
-         2 * b_elems < (1ull << 32);
-}
-
-// The large-tile kernel applies to bf16 operands whose contraction range splits into
-// multiples of 32, with M and N multiples of 8, and whose byte offsets within an
-// operand fit the 32-bit offsets of the copies.
-bool gemm_big_ok(int M, int N, int K, int k_chunk, size_t a_elems, size_t b_elems) {
-  return K % kGK == 0 && k_chunk % kGK == 0 && M % 8 == 0 && N % 8 == 0 && M >= 8 && N >= 8 &&
-         2 * a_elems < (1ull << 32) && 2 * b_elems < (1ull << 32);
-}
+// The streamed kernel applies to whole column tiles (the last row tile may be partial)
+// and at least kStreamStoreStages stages per tile.
+bool gemm_stream_ok(int N, int K) { return N % 256 == 0 && K % kGK == 0 && K / kGK >= kStreamStoreStages; }
 
 // dst[i] = sum_{s < nsplit} src[s * stride + i], in ascending s (float4 granularity).
 __global__ __launch_bounds__(256) void split_reduce_kernel(const float* __restrict__ src, float* __restrict__ dst,
@@ -822,41 +708,72 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const float* __restri
 }
 
 template <typename T> struct GemmCfg;
-template <> struct GemmCfg<bf16> { static constexpr int BM = 128, BN = 128, BK = 32; };
 template <> struct GemmCfg<float> { static constexpr int BM = 64, BN = 64, BK = 16; };
 
 inline int grid_tiles(int M, int N, int BM, int BN) { return ((M + BM - 1) / BM) * ((N + BN - 1) / BN); }
-constexpr int kCUs = 256;  // compute units of the gfx950 part (one streamed workgroup each)
+constexpr int kCUs = 256;  // compute units of the gfx950 part (one large-tile workgroup each)
+
+// bf16 tile shapes of gemm_ring_kernel: "large" (the caller's BM x BN, 65536 outputs),
+// 256 x 128 (both eight waves, one workgroup per CU) and 128 x 128 (four waves, two
+// workgroups per CU). The larger a tile, the less operand traffic per product, but fewer
+// than kRingMinGroups workgroups leave CUs idle: the largest shape that gives them is
+// launched, else 128 x 128. Measured (us, large / 256 x 128 / 128 x 128, workgroups):
+//   dW, 16 heads, d_c 512:  1000 tokens 36 (64) / 23 (128) / 20 (256);  2048 tokens 38 (128) /
+//     30 (256) / 36 (512);  5001 tokens 59 (160) / 63 (320) / 69 (640);  16384 tokens 128 (256) /
+//     137 (512) / 192 (1024)
+//   y = out W_o (F = 16384, D = 7168):  300 tokens 306 (56) / 188 (112) / 136 (168);  1000 tokens
+//     309 (112) / 246 (224) / 328 (448);  2048 tokens 419 (224) / 563 (448) / 697 (896)
+constexpr int kRingMinGroups = 160;
+
+// C = A B over nz contraction ranges of k_chunk (C + z * M * N for range z); LBM x LBN: the large tile
+template <int LBM, int LBN, bool A_KS, bool B_KS, int SPLIT, typename TO>
+void launch_ring(const bf16* A, const bf16* B, const bf16* X2, TO* C, int M, int N, int K, int lda, int ldb, int ldc,
+                 int k_chunk, int nz, hipStream_t st) {
+  constexpr int NS = SPLIT ? 3 : 4;  // ring depth (LDS: at most 144 KB, 72 KB for 128 x 128)
+  const long long stride = (long long)M * N;
+  const int nl = grid_tiles(M, N, LBM, LBN), nm = grid_tiles(M, N, 256, 128);
+  if (nl * nz >= kRingMinGroups)
+    gemm_ring_kernel<LBM, LBN, 8, (LBM <= LBN ? 2 : 4), NS, A_KS, B_KS, SPLIT, TO><<<dim3(nl, 1, nz), 512, 0, st>>>(
+        A, B, X2, C, M, N, K, lda, ldb, ldc, k_chunk, stride);
+  else if (nm * nz >= kRingMinGroups)
+    gemm_ring_kernel<256, 128, 8, 4, NS, A_KS, B_KS, SPLIT, TO><<<dim3(nm, 1, nz), 512, 0, st>>>(
+        A, B, X2, C, M, N, K, lda, ldb, ldc, k_chunk, stride);
+  else
+    gemm_ring_kernel<128, 128, 4, 2, NS, A_KS, B_KS, SPLIT, TO><<<dim3(grid_tiles(M, N, 128, 128), 1, nz), 256, 0, st>>>(
+        A, B, X2, C, M, N, K, lda, ldb, ldc, k_chunk, stride);
+}
 
 }  // namespace
 
 template <typename T>
 hipError_t launch_reconstruct(const T* c, const T* w, T* kv, int M, int N, int K, hipStream_t st) {
-  using G = GemmCfg<T>;
   if constexpr (sizeof(T) == 2) {
-    if (gemm_stream_ok(M, N, K, (size_t)M * K, (size_t)K * N)) {
-      const int tiles = grid_tiles(M, N, 256, 256);
-      gemm_stream_kernel<256, 256, false, true><<<tiles < kCUs ? tiles : kCUs, 512, 0, st>>>(
-          c, w, kv, M, N, K, /*lda=*/K, /*ldb=*/N, /*ldc=*/N);
-      return hipGetLastError();
+    // The persistent kernel where a tile's stores weigh as much as its products (short
+    // contractions) and its last round of 256 x 256 tiles leaves at most a quarter of the
+    // CUs idle. Measured (us, persistent / the ring's best; N = 4096, K = 512): 2048 rows
+    // (128 tiles) 23 / 17, 4096 rows (256) 27 / 28, 5001 rows (320) 45 / 38, 8192 rows (512)
+    // 45 / 53, 16384 rows 76 / 102; 8192 rows over K = 1024 72 / 75, over K = 2048 124 / 123,
+    // over K = 4096 227 / 222; N = 7168, K = 16384: 2048 rows 450 / 419.
+    const int tiles = grid_tiles(M, N, 256, 256), rounds = (tiles + kCUs - 1) / kCUs;
+    if (gemm_stream_ok(N, K) && K <= kStreamMaxK && 3 * rounds * kCUs <= 4 * tiles) {
+      const dim3 grid(tiles < kCUs ? tiles : kCUs);
+      if (M % 256 == 0)
+        gemm_stream_kernel<256, 256, false, true, false><<<grid, 512, 0, st>>>(c, w, kv, M, N, K, /*lda=*/K, /*ldb=*/N,
+                                                                              /*ldc=*/N);
+      else
+        gemm_stream_kernel<256, 256, false, true, true><<<grid, 512, 0, st>>>(c, w, kv, M, N, K, /*lda=*/K, /*ldb=*/N,
+                                                                             /*ldc=*/N);
+    } else {
+      launch_ring<256, 256, false, true, 0, bf16>(c, w, nullptr, kv, M, N, K, /*lda=*/K, /*ldb=*/N, /*ldc=*/N,
+                                                  /*k_chunk=*/K, 1, st);
     }
-    if (gemm_big_ok(M, N, K, K, (size_t)M * K, (size_t)K * N)) {
-      gemm_big_kernel<256, 256, false, true, 0, bf16><<<grid_tiles(M, N, 256, 256), 256, 0, st>>>(
-          c, w, nullptr, kv, M, N, K, /*lda=*/K, /*ldb=*/N, /*ldc=*/N, /*k_chunk=*/K, 0);
-      return hipGetLastError();
-    }
+  } else {
+    using G = GemmCfg<T>;
+    gemm_kernel<T, T, false, true, G::BM, G::BN, G::BK><<<grid_tiles(M, N, G::BM, G::BN), kThreads, 0, st>>>(
+        c, w, kv, M, N, K, /*lda=*/K, /*ldb=*/N, /*ldc=*/N, /*k_chunk=*/K, 0);
   }
-  dim3 grid(grid_tiles(M, N, G::BM, G::BN), 1, 1);
-  gemm_kernel<T, T, false, true, G::BM, G::BN, G::BK, 0><<<grid, kThreads, 0, st>>>(
-      c, w, nullptr, kv, M, N, K, /*lda=*/K, /*ldb=*/N, /*ldc=*/N, /*k_chunk=*/K, 0);
   return hipGetLastError();
 }
-
-namespace {
-constexpr int kMinGemmBlocks = 512;  // workgroups wanted per GEMM launch (256 CUs)
-// dc's output has d_c columns: a side of more than 256 takes 128 x 512 tiles (dKV read once)
-inline int dc_bm(int d_c) { return d_c > 256 ? 128 : 256; }
-}  // namespace
 
 int dw_split_tokens(int tokens) {
   int s = 2048;
@@ -867,19 +784,33 @@ size_t dw_split_count(int tokens) {
   const int s = dw_split_tokens(tokens);
   return (size_t)((tokens + s - 1) / s);
 }
+
+namespace {
+// dc's tiles: 128 x 128 (two workgroups per CU) while they fill the CUs no more than about
+// once, with the contraction split where they don't (at least 512 indices per split); beyond,
+// 128 x 512 (256 x 256 for d_c <= 256: the whole d_c side, so dKV is read once) over as many
+// splits as fit the CUs and the partials of dW (so that dc adds nothing to the workspace).
+// Measured (us with the reduction, 16 heads, d_c 512; 128 x 128 / 128 x 512, its splits in
+// brackets): 1000 tokens 20 (8) / 31 (16), 2048 27 (4) / 38 (8), 4096 43 (2) / 50 (8), 8192
+// 68 (1) / 76 (4), 10002 112 (1) / 96 (2), 16384 159 (1) / 135 (2).
+size_t dw_partial_elems(int tokens, int d_c, int K) {
+  return dw_split_count(tokens) > 1 ? dw_split_count(tokens) * (size_t)d_c * K : 0;
+}
+bool dc_wide(int tokens, int d_c) { return grid_tiles(tokens, d_c, 128, 128) > kCUs + kCUs / 8; }
+}  // namespace
+
 int dc_split_count(int tokens, int d_c, int K) {
-  const bool big = gemm_big_ok(tokens, d_c, K, kGK, (size_t)tokens * K, (size_t)d_c * K);
-  const int tiles = big ? grid_tiles(tokens, d_c, dc_bm(d_c), 65536 / dc_bm(d_c))
-                        : grid_tiles(tokens, d_c, GemmCfg<bf16>::BM, GemmCfg<bf16>::BN);
-  // at least 256 contraction indices (one 192/128-wide head) per split, and one split
-  const int max_split = K >= 512 ? K / 256 : 1;
-  // large tiles: one workgroup per CU (256) is enough; small tiles want two or more
-  const int want = big ? 256 : kMinGemmBlocks;
-  int n = (want + tiles - 1) / tiles;
+  const bool wide = dc_wide(tokens, d_c);
+  const int tiles = !wide       ? grid_tiles(tokens, d_c, 128, 128)
+                    : d_c > 256 ? grid_tiles(tokens, d_c, 128, 512)
+                                : grid_tiles(tokens, d_c, 256, 256);
+  const int max_split = K >= 1024 ? K / 512 : 1;
+  int n = kCUs / tiles;
+  if (wide) n = min(n, (int)(dw_partial_elems(tokens, d_c, K) / ((size_t)tokens * d_c)));
   return n < 1 ? 1 : (n > max_split ? max_split : n);
 }
 size_t gemm_partial_elems(int tokens, int d_c, int K) {
-  const size_t dw = dw_split_count(tokens) > 1 ? dw_split_count(tokens) * (size_t)d_c * K : 0;
+  const size_t dw = dw_partial_elems(tokens, d_c, K);
   const int ndc = dc_split_count(tokens, d_c, K);
   const size_t dc = ndc > 1 ? (size_t)ndc * tokens * d_c : 0;
   return dw > dc ? dw : dc;
@@ -890,33 +821,32 @@ hipError_t launch_dc(const T* dkv, const T* dkv_lo, const T* w, float* dc, float
                      hipStream_t st) {
   // dc[M=tokens][N=d_c] = (dKV + dKV_lo)[M][K=H*dkvh] @ W^T ; W stored [N][K] (k-contiguous).
   // With a split contraction each split writes its partial and a fixed-order reduce sums them.
-  using G = GemmCfg<T>;
-  const int nsplit = sizeof(T) == 2 ? dc_split_count(M, N, K) : 1;
-  const int k_chunk = (K / nsplit + G::BK - 1) / G::BK * G::BK;
-  const int nz = (K + k_chunk - 1) / k_chunk;
-  float* target = nz == 1 ? dc : partial;
-  dim3 grid(grid_tiles(M, N, G::BM, G::BN), 1, nz);
   if constexpr (sizeof(T) == 2) {
-    if (dkv_lo && gemm_big_ok(M, N, K, k_chunk, (size_t)M * K, (size_t)N * K)) {
-      if (dc_bm(N) == 128)
-        gemm_big8_kernel<128, 512, false, false, 1, float><<<dim3(grid_tiles(M, N, 128, 512), 1, nz), 512, 0, st>>>(
-            dkv, w, dkv_lo, target, M, N, K, K, K, N, k_chunk, (long long)M * N);
-      else
-        gemm_big8_kernel<256, 256, false, false, 1, float><<<dim3(grid_tiles(M, N, 256, 256), 1, nz), 512, 0, st>>>(
-            dkv, w, dkv_lo, target, M, N, K, K, K, N, k_chunk, (long long)M * N);
-      grid.x = 0;  // done
+    const int nsplit = dc_split_count(M, N, K);
+    const int k_chunk = (K / nsplit + kGK - 1) / kGK * kGK;
+    const int nz = (K + k_chunk - 1) / k_chunk;
+    float* target = nz == 1 ? dc : partial;
+    const long long stride = (long long)M * N;
+    if (!dc_wide(M, N))
+      gemm_ring_kernel<128, 128, 4, 2, 3, false, false, 1, float><<<dim3(grid_tiles(M, N, 128, 128), 1, nz), 256, 0,
+                                                                     st>>>(dkv, w, dkv_lo, target, M, N, K, K, K, N,
+                                                                           k_chunk, stride);
+    else if (N > 256)
+      gemm_ring_kernel<128, 512, 8, 2, 3, false, false, 1, float><<<dim3(grid_tiles(M, N, 128, 512), 1, nz), 512, 0,
+                                                                     st>>>(dkv, w, dkv_lo, target, M, N, K, K, K, N,
+                                                                           k_chunk, stride);
+    else
+      gemm_ring_kernel<256, 256, 8, 2, 3, false, false, 1, float><<<dim3(grid_tiles(M, N, 256, 256), 1, nz), 512, 0,
+                                                                     st>>>(dkv, w, dkv_lo, target, M, N, K, K, K, N,
+                                                                           k_chunk, stride);
+    if (nz > 1) {
+      const long long n4 = stride / 4;
+      split_reduce_kernel<<<(unsigned)((n4 + 255) / 256), 256, 0, st>>>(partial, dc, n4, nz, stride);
     }
-  }
-  if (grid.x == 0) {
-  } else if (dkv_lo)
-    gemm_kernel<T, float, false, false, G::BM, G::BN, G::BK, 1><<<grid, kThreads, 0, st>>>(
-        dkv, w, dkv_lo, target, M, N, K, K, K, N, k_chunk, (long long)M * N);
-  else
-    gemm_kernel<T, float, false, false, G::BM, G::BN, G::BK, 0><<<grid, kThreads, 0, st>>>(
-        dkv, w, nullptr, target, M, N, K, K, K, N, k_chunk, (long long)M * N);
-  if (nz > 1) {
-    const long long n4 = (long long)M * N / 4;
-    split_reduce_kernel<<<(unsigned)((n4 + 255) / 256), 256, 0, st>>>(partial, dc, n4, nz, (long long)M * N);
+  } else {
+    using G = GemmCfg<T>;
+    gemm_kernel<T, float, false, false, G::BM, G::BN, G::BK><<<grid_tiles(M, N, G::BM, G::BN), kThreads, 0, st>>>(
+        dkv, w, dc, M, N, K, K, K, N, K, 0);
   }
   return hipGetLastError();
 }
@@ -925,29 +855,20 @@ template <typename T>
 hipError_t launch_dw(const T* c, const T* dkv, const T* dkv_lo, float* dw, float* partial, int M, int N, int K,
                      hipStream_t st) {
   // dW[M=d_c][N=H*dkvh] = c^T @ (dKV + dKV_lo); c stored [K=tokens][M] and dKV [K][N]: both k-strided.
-  using G = GemmCfg<T>;
   const int split = dw_split_tokens(K);
   const int nsplit = (int)dw_split_count(K);
   float* target = nsplit == 1 ? dw : partial;
-  dim3 grid(grid_tiles(M, N, G::BM, G::BN), 1, nsplit);
   if constexpr (sizeof(T) == 2) {
-    if (dkv_lo && gemm_big_ok(M, N, K, split, (size_t)K * M, (size_t)K * N)) {
-      if (M > 256)
-        gemm_big8_kernel<512, 128, true, true, 2, float><<<dim3(grid_tiles(M, N, 512, 128), 1, nsplit), 512, 0, st>>>(
-            c, dkv, dkv_lo, target, M, N, K, M, N, N, split, (long long)M * N);
-      else
-        gemm_big8_kernel<256, 256, true, true, 2, float><<<dim3(grid_tiles(M, N, 256, 256), 1, nsplit), 512, 0, st>>>(
-            c, dkv, dkv_lo, target, M, N, K, M, N, N, split, (long long)M * N);
-      grid.x = 0;  // done
-    }
+    if (M > 256)
+      launch_ring<512, 128, true, true, 2, float>(c, dkv, dkv_lo, target, M, N, K, M, N, N, split, nsplit, st);
+    else
+      launch_ring<256, 256, true, true, 2, float>(c, dkv, dkv_lo, target, M, N, K, M, N, N, split, nsplit, st);
+  } else {
+    using G = GemmCfg<T>;
+    gemm_kernel<T, float, true, true, G::BM, G::BN, G::BK><<<dim3(grid_tiles(M, N, G::BM, G::BN), 1, nsplit), kThreads,
+                                                             0, st>>>(c, dkv, target, M, N, K, M, N, N, split,
+                                                                      (long long)M * N);
   }
-  if (grid.x == 0) {
-  } else if (dkv_lo)
-    gemm_kernel<T, float, true, true, G::BM, G::BN, G::BK, 2><<<grid, kThreads, 0, st>>>(
-        c, dkv, dkv_lo, target, M, N, K, M, N, N, split, (long long)M * N);
-  else
-    gemm_kernel<T, float, true, true, G::BM, G::BN, G::BK, 0><<<grid, kThreads, 0, st>>>(
-        c, dkv, nullptr, target, M, N, K, M, N, N, split, (long long)M * N);
   if (nsplit > 1) {
     const long long n4 = (long long)M * N / 4;
     split_reduce_kernel<<<(unsigned)((n4 + 255) / 256), 256, 0, st>>>(partial, dw, n4, nsplit, (long long)M * N);
@@ -958,23 +879,20 @@ hipError_t launch_dw(const T* c, const T* dkv, const T* dkv_lo, float* dw, float
 template <typename T>
 hipError_t launch_gemm_nt(const T* a, const T* w, T* c, int M, int N, int K, hipStream_t st) {
   // c[M][N] = a[M][K] @ w^T, w stored [N][K] (both k-contiguous); element-dtype output
-  using G = GemmCfg<T>;
   if constexpr (sizeof(T) == 2) {
-    if (gemm_big_ok(M, N, K, K, (size_t)M * K, (size_t)N * K)) {
-      gemm_big8_kernel<256, 256, false, false, 0, bf16><<<grid_tiles(M, N, 256, 256), 512, 0, st>>>(
-          a, w, nullptr, c, M, N, K, K, K, N, K, 0);
-      return hipGetLastError();
-    }
+    launch_ring<256, 256, false, false, 0, bf16>(a, w, nullptr, c, M, N, K, K, K, N, K, 1, st);
+  } else {
+    using G = GemmCfg<T>;
+    gemm_kernel<T, T, false, false, G::BM, G::BN, G::BK><<<grid_tiles(M, N, G::BM, G::BN), kThreads, 0, st>>>(
+        a, w, c, M, N, K, K, K, N, K, 0);
   }
-  gemm_kernel<T, T, false, false, G::BM, G::BN, G::BK, 0><<<dim3(grid_tiles(M, N, G::BM, G::BN), 1, 1), kThreads,
-                                                              0, st>>>(a, w, nullptr, c, M, N, K, K, K, N, K, 0);
   return hipGetLastError();
 }
 
 int gemm_tn_splits(int M, int N, int K, int esize) {
-  const bool big = esize == 2 && gemm_big_ok(M, N, K, kGK, (size_t)K * M, (size_t)K * N);
-  const int tiles = big ? grid_tiles(M, N, 256, 256) : grid_tiles(M, N, GemmCfg<bf16>::BM, GemmCfg<bf16>::BN);
-  const int want = big ? 256 : kMinGemmBlocks;
+  const bool large = esize == 2 && K % kGK == 0;
+  const int tiles = large ? grid_tiles(M, N, 256, 256) : grid_tiles(M, N, 128, 128);
+  const int want = large ? kCUs : 2 * kCUs;
   int n = (want + tiles - 1) / tiles;
   const int max_split = (K + 511) / 512;
   return n < 1 ? 1 : (n > max_split ? max_split : n);
@@ -985,22 +903,17 @@ hipError_t launch_gemm_tn(const T* a, const T* b, float* c, float* partial, int 
                           hipStream_t st) {
   // c[M][N] = a^T @ b with a stored [K][M] and b [K][N] (both k-strided), fp32 output; the
   // contraction split into nsplit ranges of whole 32-index stages, summed in ascending order
-  using G = GemmCfg<T>;
   const int split = ((K + nsplit - 1) / nsplit + 31) / 32 * 32;
   const int nz = (K + split - 1) / split;
   float* target = nz == 1 ? c : partial;
-  bool done = false;
   if constexpr (sizeof(T) == 2) {
-    if (gemm_big_ok(M, N, K, split, (size_t)K * M, (size_t)K * N)) {
-      gemm_big8_kernel<256, 256, true, true, 0, float><<<dim3(grid_tiles(M, N, 256, 256), 1, nz), 512, 0, st>>>(
-          a, b, nullptr, target, M, N, K, M, N, N, split, (long long)M * N);
-      done = true;
-    }
+    launch_ring<256, 256, true, true, 0, float>(a, b, nullptr, target, M, N, K, M, N, N, split, nz, st);
+  } else {
+    using G = GemmCfg<T>;
+    gemm_kernel<T, float, true, true, G::BM, G::BN, G::BK><<<dim3(grid_tiles(M, N, G::BM, G::BN), 1, nz), kThreads, 0,
+                                                             st>>>(a, b, target, M, N, K, M, N, N, split,
+                                                                   (long long)M * N);
   }
-  if (!done)
-    gemm_kernel<T, float, true, true, G::BM, G::BN, G::BK, 0><<<dim3(grid_tiles(M, N, G::BM, G::BN), 1, nz),
-                                                                kThreads, 0, st>>>(
-        a, b, nullptr, target, M, N, K, M, N, N, split, (long long)M * N);
   if (nz > 1) {
     const long long n4 = (long long)M * N / 4;
     split_reduce_kernel<<<(unsigned)((n4 + 255) / 256), 256, 0, st>>>(partial, c, n4, nz, (long long)M * N);
