@@ -19,7 +19,8 @@ BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "liblaga.so")
 ARCH = "gfx950"
 
-SOURCES = ["api.hip", "gemm.hip", "attn_fwd.hip", "attn_bwd.hip", "attn_bwd_kv.hip", "attn_bwd_dq.hip", "prologue.hip"]
+SOURCES = ["api.hip", "gemm.hip", "attn_fwd.hip", "attn_fwd_half.hip", "attn_bwd.hip", "attn_bwd_kv.hip",
+           "attn_bwd_half.hip", "attn_bwd_dq.hip", "attn_bwd_dq_half.hip", "prologue.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -34,11 +35,9 @@ FLAGS = [
 
 # Per-file code-generation choices (measured: with MFMA results kept in VGPRs the
 # softmax / dZ arithmetic on the accumulators needs no AGPR<->VGPR copies).
-EXTRA = {
-    "attn_fwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
-    "attn_bwd_dq.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
-    "attn_bwd_kv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
-}
+EXTRA = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
+         for f in ("attn_fwd.hip", "attn_fwd_half.hip", "attn_bwd_dq.hip", "attn_bwd_dq_half.hip", "attn_bwd_kv.hip",
+                   "attn_bwd_half.hip")}
 
 
 def _compile(src: str) -> str:

@@ -582,6 +582,8 @@ hipError_t launch_attn_bwd(const AttnBwdArgs& a, int stage, hipStream_t st) {
         if (a.ds) dkdv32_kernel<DN, DR, DV, true, false><<<grid, 256, 0, st>>>(P);
         else dkdv32_kernel<DN, DR, DV, false, false><<<grid, 256, 0, st>>>(P);
       }
+    } else if constexpr (sizeof(T) == 2 && DN == 64) {
+      return launch_dkdv_half(P, a.B, st);
     } else {
       return launch_dkdv_generic<T, DN, DR, DV>(P, a.B, st);
     }

@@ -184,12 +184,12 @@ __global__ __launch_bounds__(64 * WPH) void dq_kernel(BwdParams P) {
 // same exp2 argument, dS rounded once to bf16) and dQ sums the keys in ascending
 // 16-wide steps, as the pass over the stored dS^T does: dq is bitwise equal to it.
 template <int DN, int DR, int DV, int NW>
-__global__ __launch_bounds__(64 * NW, 1) void dq_rec_kernel(BwdParams P) {
+__global__ __launch_bounds__(64 * NW, DN == 128 ? 1 : 2) void dq_rec_kernel(BwdParams P) {
   using T = bf16;
   constexpr int DQK = DN + DR, DKVH = DN + DV, BC = 64, BR = 32 * NW;
   constexpr int KCPR = DN / 8, PCPR = DR / 8, VCPR = DV / 8;
   constexpr int NKS = DQK / 16, NVS = DV / 16, NDB = DQK / 32, NDN = DN / 32;
-  static_assert(KCPR == 16 && PCPR == 8 && VCPR == 16, "swizzles are defined for 128/64/128-wide rows");
+  static_assert(KCPR == VCPR && (KCPR == 16 || KCPR == 8) && (PCPR == 8 || PCPR == 4), "swizzled row widths");
   // two ring stages as distinct LDS objects (compile-time stage offsets in the reads)
   __shared__ __attribute__((aligned(16))) T sK0[BC * DN], sK1[BC * DN];
   __shared__ __attribute__((aligned(16))) T sP0[BC * DR], sP1[BC * DR];
@@ -274,17 +274,17 @@ __global__ __launch_bounds__(64 * NW, 1) void dq_rec_kernel(BwdParams P) {
     const bool need_mask = (P.causal && kt + BC - 1 > q0) || (kt + BC > S);
 #pragma unroll
     for (int kb = 0; kb < BC / 32; ++kb) {
-      // product i of S^T (even i < 16 and i >= 16: contraction step a_ks(i) of K) and of
-      // dP^T (odd i < 16: step i / 2 of V), alternating accumulators
-      auto a_is_s = [](int i) { return i >= 16 || (i & 1) == 0; };
-      auto a_ks = [](int i) { return i >= 16 ? 8 + (i - 16) : i >> 1; };
+      // product i of S^T (even i < 2 NVS and i >= 2 NVS: contraction step a_ks(i) of K) and
+      // of dP^T (odd i < 2 NVS: step i / 2 of V), alternating accumulators
+      auto a_is_s = [](int i) { return i >= 2 * NVS || (i & 1) == 0; };
+      auto a_ks = [](int i) { return i >= 2 * NVS ? i - NVS : i >> 1; };
       auto a_frag = [&](int i) {
         const int ks = a_ks(i), row = kb * 32 + n;
         if (!a_is_s(i)) return swz_frag<T, VCPR>(tv, row, 2 * ks + g);
         return ks < DN / 16 ? swz_frag<T, KCPR>(tk, row, 2 * ks + g)
                             : swz_frag<T, PCPR>(tp, row, 2 * (ks - DN / 16) + g);
       };
-      constexpr int NA = NKS + NVS;  // 20 products
+      constexpr int NA = NKS + NVS;  // 20 products at 192/128-wide heads
       f32x16 sa, dp;
       {
         frag_t<T> ab[PF + 1];
@@ -324,7 +324,7 @@ __global__ __launch_bounds__(64 * NW, 1) void dq_rec_kernel(BwdParams P) {
         return db < NDN ? swz_tr_frag<KCPR>(tk, ra, ra + 8, db * 32)
                         : swz_tr_frag<PCPR>(tp, ra, ra + 8, (db - NDN) * 32);
       };
-      constexpr int NQ = 2 * NDB;  // 12 products
+      constexpr int NQ = 2 * NDB;
       {
         frag_t<T> kb_[PF + 1];
 #pragma unroll
@@ -846,7 +846,7 @@ hipError_t launch_bwd_dq(bwd::BwdParams P, int B, hipStream_t st) {
       return hipGetLastError();
     }
   }
-  if constexpr (sizeof(T) == 2 && DN == 128 && DR == 64 && DV == 128) {
+  if constexpr (sizeof(T) == 2 && DN >= 64) {
     // no dS^T store: recompute S, P, dP and dS per key tile
     constexpr int RW = DQ_REC_WAVES;
     P.n_blocks = (P.S + 32 * RW - 1) / (32 * RW);
@@ -858,11 +858,14 @@ hipError_t launch_bwd_dq(bwd::BwdParams P, int B, hipStream_t st) {
 }
 
 #define LAGA_INST_DQ(T, DN, DR, DV) template hipError_t launch_bwd_dq<T, DN, DR, DV>(bwd::BwdParams, int, hipStream_t);
+#ifndef LAGA_HALF_WIDTHS
 LAGA_INST_DQ(bf16, 128, 64, 128)
 LAGA_INST_DQ(float, 128, 64, 128)
 LAGA_INST_DQ(bf16, 32, 16, 32)
 LAGA_INST_DQ(float, 32, 16, 32)
+#else
 LAGA_INST_DQ(bf16, 64, 32, 64)
 LAGA_INST_DQ(float, 64, 32, 64)
+#endif
 
 }  // namespace laga

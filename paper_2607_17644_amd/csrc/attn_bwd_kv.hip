@@ -229,10 +229,9 @@ hipError_t launch_dkdv_generic(BwdParams P, int B, hipStream_t st) {
 
 #define LAGA_INST_DKDV(T, DN, DR, DV) \
   template hipError_t launch_dkdv_generic<T, DN, DR, DV>(BwdParams, int, hipStream_t);
-LAGA_INST_DKDV(float, 128, 64, 128)  // bf16 at these widths runs dkdv32_kernel
+LAGA_INST_DKDV(float, 128, 64, 128)  // bf16 at these widths runs dkdv32_kernel, at 64/32/64 dkdv_half_kernel
 LAGA_INST_DKDV(bf16, 32, 16, 32)
 LAGA_INST_DKDV(float, 32, 16, 32)
-LAGA_INST_DKDV(bf16, 64, 32, 64)
 LAGA_INST_DKDV(float, 64, 32, 64)
 
 }  // namespace laga

@@ -271,7 +271,7 @@ void attn_fwd_kernel(FwdParams P) {
 
 
 // ------------------------------------------------------------------ ring variant
-// bf16 forward for 128-wide K_nope / V and 64-wide k_pe. Key tiles stream through a
+// bf16 forward for 128-wide K_nope / V and 64-wide k_pe, or half of each. Key tiles stream through a
 // two-stage LDS ring filled by direct global->LDS loads into swizzled, unpadded
 // tiles (no staging registers, one barrier per tile). There is no per-wave branch
 // around the MFMAs: a wave whose queries all precede a tile runs it fully masked
@@ -286,7 +286,7 @@ __global__ __launch_bounds__(64 * WPH) void attn_fwd_ring_kernel(FwdParams P) {
   using T = bf16;
   constexpr int DQK = DN + DR, DKVH = DN + DV, NW = WPH, WH = WPH / G, BR = 32 * WH;
   constexpr int KCPR = DN / 8, PCPR = DR / 8, VCPR = DV / 8;
-  static_assert(KCPR == 16 && PCPR == 8 && VCPR == 16, "swizzles are defined for 128/64/128-wide rows");
+  static_assert(KCPR == VCPR && (KCPR == 16 || KCPR == 8) && (PCPR == 8 || PCPR == 4), "swizzled row widths");
   static_assert(WPH % G == 0, "whole waves per head");
   // two ring stages as distinct LDS objects: the compiler then sees that the direct
   // loads into one stage cannot alias the reads of the other and does not wait for
@@ -757,18 +757,24 @@ hipError_t launch_attn_fwd(const AttnFwdArgs& a, hipStream_t st) {
   P.scale_log2 = a.scale * 1.4426950408889634f;
   P.causal = a.causal;
   dim3 grid(P.n_qblocks * P.n_hgroups, a.B, 1);
-  if constexpr (sizeof(T) == 2 && DN == 128 && DR == 64 && DV == 128 && Tl::G == 1) {
+  if constexpr (sizeof(T) == 2 && DN >= 64 && Tl::G == 1) {
     // 8 waves: 256 queries of one head per workgroup, which halves the K/V tile
     // traffic of 4 waves (measured 8 % faster at S = 16384); 4 waves when 8 would leave
-    // fewer than kFwdFillGroups workgroups (few heads or short sequences)
+    // fewer than kFwdFillGroups workgroups (few heads or short sequences). Half-width heads
+    // (158 registers: three waves per SIMD) always take 4: three workgroups fit a CU, one
+    // of 8 waves does (4 x 2000 tokens, 16 heads: 76 us against 96 us)
     auto ring = [&](auto rw) {
       constexpr int RW = decltype(rw)::value, RG = kFwdRingHeads, RBR = 32 * RW / RG;
       P.n_qblocks = (a.S + RBR - 1) / RBR;
       P.n_hgroups = (a.H + RG - 1) / RG;
       attn_fwd_ring_kernel<DN, DR, DV, Tl::BC, RW, RG><<<dim3(P.n_qblocks * P.n_hgroups, a.B, 1), 64 * RW, 0, st>>>(P);
     };
-    if ((long long)((a.S + 255) / 256) * P.n_hgroups * a.B >= kFwdFillGroups) ring(std::integral_constant<int, 8>{});
-    else ring(std::integral_constant<int, 4>{});
+    if constexpr (DN == 128) {
+      if ((long long)((a.S + 255) / 256) * P.n_hgroups * a.B >= kFwdFillGroups) ring(std::integral_constant<int, 8>{});
+      else ring(std::integral_constant<int, 4>{});
+    } else {
+      ring(std::integral_constant<int, 4>{});
+    }
   } else {
     using Cfg = FwdCfg<T, DN, DR, DV, Tl::BC, Tl::WPH, Tl::G, false>;
     attn_fwd_kernel<T, DN, DR, DV, Tl::BC, Tl::WPH, Tl::G, false><<<grid, Cfg::NT, 0, st>>>(P);
@@ -800,6 +806,7 @@ hipError_t launch_attn_fwd_fused(const AttnFwdArgs& a, void* w_t_ws, hipStream_t
   return hipGetLastError();
 }
 
+#ifndef LAGA_HALF_WIDTHS
 template <typename T>
 hipError_t launch_frag_w_pi(const T* w, T* w_t, int K, int N, hipStream_t st) {
   const long long nw = (long long)K * N;
@@ -807,15 +814,19 @@ hipError_t launch_frag_w_pi(const T* w, T* w_t, int K, int N, hipStream_t st) {
   return hipGetLastError();
 }
 template hipError_t launch_frag_w_pi<bf16>(const bf16*, bf16*, int, int, hipStream_t);
+#endif
 
 #define LAGA_INST_FWD(T, DN, DR, DV)                                                      \
   template hipError_t launch_attn_fwd<T, DN, DR, DV>(const AttnFwdArgs&, hipStream_t);    \
   template hipError_t launch_attn_fwd_fused<T, DN, DR, DV>(const AttnFwdArgs&, void*, hipStream_t);
+#ifndef LAGA_HALF_WIDTHS
 LAGA_INST_FWD(bf16, 128, 64, 128)
 LAGA_INST_FWD(float, 128, 64, 128)
 LAGA_INST_FWD(bf16, 32, 16, 32)
 LAGA_INST_FWD(float, 32, 16, 32)
+#else
 LAGA_INST_FWD(bf16, 64, 32, 64)
 LAGA_INST_FWD(float, 64, 32, 64)
+#endif
 
 }  // namespace laga

@@ -222,6 +222,7 @@ template <> __device__ __forceinline__ int swz<24>(int r) {
 template <> __device__ __forceinline__ int swz<8>(int r) {
   return ((r & 2) << 1) | ((r & 4) >> 1) | ((r >> 3) & 1);
 }
+template <> __device__ __forceinline__ int swz<4>(int r) { return (r >> 2) & 3; }
 
 // Element offset of (row, element col) in a swizzled tile of CPR chunks per row.
 template <typename T, int CPR>
@@ -301,17 +302,17 @@ __device__ __forceinline__ bf16x8 pad_tr_frag(const bf16* tile, int ra, int rb, 
   return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// Swizzled-tile fill with the per-lane address arithmetic hoisted. For CPR = 8 or 16 a
+// Swizzled-tile fill with the per-lane address arithmetic hoisted. For CPR = 4, 8 or 16 a
 // load instruction covers 64 / CPR whole rows, and the swizzle depends on the row bits
 // that the instruction index sets only through its residue modulo 2 (CPR 8) or 4
-// (CPR 16); with NW a multiple of that, a lane's chunk permutation is the same in
+// (CPR 16; CPR 4: not at all); with NW a multiple of that, a lane's chunk permutation is the same in
 // every instruction of its wave. So init() computes one element offset per lane, and
 // a fill adds a wave-uniform row offset per instruction. Rows sit at a fixed element
 // stride in global memory; a tile that crosses the end of the data (rows_valid <
 // NROWS) takes the general path, clamping rows to rows_valid - 1.
 template <typename T, int NROWS, int CPR, int NW>
 struct SwzRowFill {
-  static_assert(CPR == 8 || CPR == 16, "whole rows per load instruction");
+  static_assert(CPR == 4 || CPR == 8 || CPR == 16, "whole rows per load instruction");
   static constexpr int E = 16 / sizeof(T), RPI = 64 / CPR, NI = NROWS * CPR / 64;
   static_assert(NI * 64 == NROWS * CPR && NW % (CPR == 16 ? 4 : 2) == 0, "uniform chunk permutation per wave");
   int lane_off;
@@ -351,6 +352,21 @@ __device__ __forceinline__ int xcd_remap(int id, int n) {
   constexpr int kXcd = 8;
   if (n % kXcd) return id;
   return (id % kXcd) * (n / kXcd) + id / kXcd;
+}
+
+// Workgroup id -> (head bh of BH = B * H, block blk of nblk), blocks in ascending order over
+// every head of the XCD that the id lands on. With the causal mask a head's blocks differ in
+// work; the caller numbers them heaviest first, so each XCD starts the heavy blocks of all
+// its heads before the light ones, which then fill the gaps at the end (longest job first).
+__device__ __forceinline__ void heavy_first(int id, int nblk, int BH, int& bh, int& blk) {
+  if (BH % 8 == 0) {  // each XCD (id % 8) keeps BH / 8 whole heads, for its L2
+    const int hp = BH / 8, i = id / 8;
+    bh = (id % 8) * hp + i % hp;
+    blk = i / hp;
+  } else {
+    bh = id % BH;
+    blk = id / BH;
+  }
 }
 
 }  // namespace laga
