@@ -146,10 +146,8 @@ __global__ __launch_bounds__(256, 1) void dkdv32_kernel(BwdParams P) {
   const T* __restrict__ dout = (const T*)P.dout;
   const int S = P.S, H = P.H;
 
-  const int total = P.n_blocks * H * gridDim.y;
-  const int lin = xcd_remap(blockIdx.x + gridDim.x * blockIdx.y, total);
-  const int kb = lin % P.n_blocks;
-  const int bh = lin / P.n_blocks;
+  int bh, kb;  // the first key blocks see the most queries
+  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_blocks, H * gridDim.y, bh, kb);
   const int b = bh / H, h = bh % H;
 
   const int tid = threadIdx.x, l = tid & 63, n = l & 31, g = l >> 5;

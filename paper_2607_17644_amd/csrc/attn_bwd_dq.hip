@@ -34,10 +34,9 @@ __global__ __launch_bounds__(64 * WPH) void dq_kernel(BwdParams P) {
   const T* __restrict__ dout = (const T*)P.dout;
   const int S = P.S, H = P.H;
 
-  const int total = P.n_blocks * H * gridDim.y;
-  const int lin = xcd_remap(blockIdx.x + gridDim.x * blockIdx.y, total);
-  const int qblk = P.n_blocks - 1 - lin % P.n_blocks;  // heavy first
-  const int bh = lin / P.n_blocks;
+  int bh, qblk;
+  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_blocks, H * gridDim.y, bh, qblk);
+  qblk = P.n_blocks - 1 - qblk;
   const int b = bh / H, h = bh % H;
 
   const int tid = threadIdx.x, wave = tid >> 6, l = tid & 63, n = l & 31, g = l >> 5;
@@ -201,10 +200,9 @@ __global__ __launch_bounds__(64 * NW, DN == 128 ? 1 : 2) void dq_rec_kernel(BwdP
   const T* __restrict__ dout = (const T*)P.dout;
   const int S = P.S, H = P.H;
 
-  const int total = P.n_blocks * H * gridDim.y;
-  const int lin = xcd_remap(blockIdx.x + gridDim.x * blockIdx.y, total);
-  const int qblk = P.n_blocks - 1 - lin % P.n_blocks;  // heavy first
-  const int bh = lin / P.n_blocks;
+  int bh, qblk;
+  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_blocks, H * gridDim.y, bh, qblk);
+  qblk = P.n_blocks - 1 - qblk;
   const int b = bh / H, h = bh % H;
 
   const int tid = threadIdx.x, l = tid & 63, n = l & 31, g = l >> 5;
@@ -387,10 +385,9 @@ __global__ __launch_bounds__(64 * WPH, 1) void dq_ds_kernel(BwdParams P) {
   const T* __restrict__ ds = (const T*)P.ds;
   const int S = P.S, H = P.H, TT = P.ds_T;
 
-  const int total = P.n_blocks * H * gridDim.y;
-  const int lin = xcd_remap(blockIdx.x + gridDim.x * blockIdx.y, total);
-  const int qblk = P.n_blocks - 1 - lin % P.n_blocks;  // heavy first
-  const int bh = lin / P.n_blocks;
+  int bh, qblk;
+  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_blocks, H * gridDim.y, bh, qblk);
+  qblk = P.n_blocks - 1 - qblk;
   const int b = bh / H, h = bh % H;
 
   const int tid = threadIdx.x, wave = tid >> 6, l = tid & 63, n = l & 31, g = l >> 5;
@@ -516,10 +513,9 @@ __global__ __launch_bounds__(512, 1) void dq_ds_fused_kernel(BwdParams P) {
   const T* __restrict__ ds = (const T*)P.ds;
   const int S = P.S, H = P.H, TT = P.ds_T, dc = P.d_c;
 
-  const int total = P.n_blocks * H * gridDim.y;
-  const int lin = xcd_remap(blockIdx.x + gridDim.x * blockIdx.y, total);
-  const int qblk = P.n_blocks - 1 - lin % P.n_blocks;  // heavy first
-  const int bh = lin / P.n_blocks;
+  int bh, qblk;
+  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_blocks, H * gridDim.y, bh, qblk);
+  qblk = P.n_blocks - 1 - qblk;
   const int b = bh / H, h = bh % H;
 
   const int tid = threadIdx.x, wave = tid >> 6, l = tid & 63, n = l & 31, g = l >> 5;
@@ -638,10 +634,9 @@ __global__ __launch_bounds__(256, 1) void dq_ds_fused2_kernel(BwdParams P) {
   const T* __restrict__ ds = (const T*)P.ds;
   const int S = P.S, H = P.H, TT = P.ds_T;
 
-  const int total = P.n_blocks * H * gridDim.y;
-  const int lin = xcd_remap(blockIdx.x + gridDim.x * blockIdx.y, total);
-  const int qblk = P.n_blocks - 1 - lin % P.n_blocks;  // heavy first
-  const int bh = lin / P.n_blocks;
+  int bh, qblk;
+  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_blocks, H * gridDim.y, bh, qblk);
+  qblk = P.n_blocks - 1 - qblk;
   const int b = bh / H, h = bh % H;
 
   const int tid = threadIdx.x, l = tid & 63, n = l & 31, g = l >> 5;

@@ -160,10 +160,9 @@ void attn_fwd_kernel(FwdParams P) {
   const int S = P.S, H = P.H;
 
   // heavy-first, head-major ordering; each XCD gets a contiguous range of heads
-  const int total = P.n_qblocks * P.n_hgroups * gridDim.y;
-  const int lin = xcd_remap(blockIdx.x + gridDim.x * blockIdx.y, total);
-  const int qb = P.n_qblocks - 1 - lin % P.n_qblocks;
-  const int hgb = lin / P.n_qblocks;
+  int hgb, qb;
+  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_qblocks, P.n_hgroups * gridDim.y, hgb, qb);
+  qb = P.n_qblocks - 1 - qb;
   const int b = hgb / P.n_hgroups;
   const int h0 = (hgb % P.n_hgroups) * G;
 
@@ -300,10 +299,9 @@ __global__ __launch_bounds__(64 * WPH) void attn_fwd_ring_kernel(FwdParams P) {
   const T* __restrict__ kv = (const T*)P.kv;
   const int S = P.S, H = P.H;
 
-  const int total = P.n_qblocks * P.n_hgroups * gridDim.y;
-  const int lin = xcd_remap(blockIdx.x + gridDim.x * blockIdx.y, total);
-  const int qb = P.n_qblocks - 1 - lin % P.n_qblocks;
-  const int bhg = lin / P.n_qblocks;
+  int bhg, qb;
+  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_qblocks, P.n_hgroups * gridDim.y, bhg, qb);
+  qb = P.n_qblocks - 1 - qb;
   const int b = bhg / P.n_hgroups, h0 = (bhg % P.n_hgroups) * G;
 
   const int tid = threadIdx.x, l = tid & 63, n = l & 31, g = l >> 5;
@@ -550,10 +548,9 @@ __global__ __launch_bounds__(64 * WPH) void attn_fwd_fused_kernel(FwdFusedParams
   const T* __restrict__ wt = (const T*)P.w_t;
   const int S = P.S, H = P.H, dc = P.d_c;
 
-  const int total = P.n_qblocks * H * gridDim.y;
-  const int lin = xcd_remap(blockIdx.x + gridDim.x * blockIdx.y, total);
-  const int qb = P.n_qblocks - 1 - lin % P.n_qblocks;
-  const int bh = lin / P.n_qblocks;
+  int bh, qb;
+  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_qblocks, H * gridDim.y, bh, qb);
+  qb = P.n_qblocks - 1 - qb;
   const int b = bh / H, h = bh % H;
 
   const int tid = threadIdx.x, wave = tid >> 6, l = tid & 63, n = l & 31, g = l >> 5;
