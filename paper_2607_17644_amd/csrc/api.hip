@@ -104,7 +104,7 @@ laga_status_t from_hip(hipError_t e) { return e == hipSuccess ? LAGA_OK : LAGA_E
 // Producers: d_gamma partial rows of the backward.
 size_t prologue_ws_bytes(const Dims& d) {
   const long long tok = (long long)d.B * d.S;
-  return round_up(sizeof(float) * (size_t)(prologue_bwd_rows(tok) + prologue_sum_groups(tok)) * d.d_c);
+  return round_up(sizeof(float) * (size_t)prologue_bwd_rows(tok) * d.d_c);
 }
 
 laga_status_t validate_prologue(const laga_problem_t* p, const laga_prologue_t* cfg, Dims* d) {

@@ -133,7 +133,7 @@ struct PrologueArgs {
   float* d_latent;         // backward output [B,S,d_c]
   float* d_kpe;            // backward output [B,S,d_rope]
   float* d_gamma;          // backward output [d_c] (with gamma)
-  float* partial;          // backward workspace [prologue_bwd_rows + prologue_sum_groups][d_c] (with gamma), else NULL
+  float* partial;          // backward workspace [prologue_bwd_rows][d_c] (with gamma), else NULL
   int B, S, H, d_c, d_nope, d_rope, d_qk;
   int64_t position_offset;
   float eps;
@@ -141,8 +141,6 @@ struct PrologueArgs {
 };
 // rows of d_gamma partial sums the backward writes for `tokens` tokens
 int prologue_bwd_rows(long long tokens);
-// row groups of the fixed-order column sum of those rows
-int prologue_sum_groups(long long tokens);
 template <typename T>
 hipError_t launch_prologue_fwd(const PrologueArgs& a, hipStream_t st);
 template <typename T>

@@ -232,19 +232,36 @@ __global__ __launch_bounds__(64 * kWaves) void prologue_bwd_kernel(PrologueArgs 
   }
 }
 
-// Column sums of a [rows][cols] partial buffer in a fixed order, in two launches: row
-// group g (rows [g*rows/G, (g+1)*rows/G), ascending) of a 64-column block per wave,
-// then the G group sums of each column, ascending. One lane per column.
-constexpr int kSumGroups = 64;
-__global__ __launch_bounds__(64) void column_sum_kernel(const float* __restrict__ src, float* __restrict__ dst,
-                                                        int rows, int cols, int groups) {
-  const int j = blockIdx.x * 64 + threadIdx.x;
-  if (j >= cols) return;
-  const int g = blockIdx.y;
-  const int r0 = (int)((long long)rows * g / groups), r1 = (int)((long long)rows * (g + 1) / groups);
+// Column sums of a [rows][cols] partial buffer in a fixed order, in one launch: a workgroup
+// takes 16 columns, its 1024 threads 64 rows at a time (thread (r, c): rows r, r + 64, ... of
+// column c, ascending), then the 64 sums of a column are added in a tree. Bound by the
+// latency of its loads: eight rows per thread are in flight, so 1024 rows are two trips.
+// 1024 x 512: 4 us; two launches of one lane per column, with a load in flight each, took 22.
+constexpr int kSumCols = 16, kSumRows = 64;
+__global__ __launch_bounds__(kSumCols * kSumRows) void column_sum_kernel(const float* __restrict__ src,
+                                                                         float* __restrict__ dst, int rows, int cols) {
+  __shared__ float sm[kSumRows][kSumCols];
+  const int c = threadIdx.x % kSumCols, r = threadIdx.x / kSumCols;
+  const float* col = src + blockIdx.x * kSumCols + c;  // cols is a multiple of 32
+  constexpr int U = 8;
   float t = 0.f;
-  for (int r = r0; r < r1; ++r) t += src[(size_t)r * cols + j];
-  dst[(size_t)g * cols + j] = t;
+  for (int r0 = r; r0 < rows; r0 += U * kSumRows) {
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int rr = r0 + u * kSumRows;
+      v[u] = rr < rows ? col[(size_t)rr * cols] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) t += v[u];
+  }
+  sm[r][c] = t;
+#pragma unroll
+  for (int h = kSumRows / 2; h > 0; h /= 2) {
+    __syncthreads();
+    if (r < h) sm[r][c] += sm[r + h][c];
+  }
+  if (r == 0) dst[blockIdx.x * kSumCols + c] = sm[0][c];
 }
 
 }  // namespace
@@ -252,11 +269,6 @@ __global__ __launch_bounds__(64) void column_sum_kernel(const float* __restrict_
 int prologue_bwd_rows(long long tokens) {
   const long long per = (long long)kWaves * kBwdTokPerWave;
   return (int)((tokens + per - 1) / per);
-}
-
-int prologue_sum_groups(long long tokens) {
-  const int rows = prologue_bwd_rows(tokens);
-  return rows < kSumGroups ? rows : kSumGroups;
 }
 
 template <typename T>
@@ -272,11 +284,7 @@ hipError_t launch_prologue_bwd(const PrologueArgs& a, hipStream_t st) {
   const int rows = prologue_bwd_rows(tok);
   prologue_bwd_kernel<T><<<(unsigned)rows, 64 * kWaves, 0, st>>>(a);
   if (a.partial) {
-    // partial holds the rows, then the group sums
-    const int G = prologue_sum_groups(tok);
-    float* gsum = a.partial + (size_t)rows * a.d_c;
-    column_sum_kernel<<<dim3((a.d_c + 63) / 64, G), 64, 0, st>>>(a.partial, gsum, rows, a.d_c, G);
-    column_sum_kernel<<<dim3((a.d_c + 63) / 64, 1), 64, 0, st>>>(gsum, a.d_gamma, G, a.d_c, 1);
+    column_sum_kernel<<<a.d_c / kSumCols, kSumCols * kSumRows, 0, st>>>(a.partial, a.d_gamma, rows, a.d_c);
   }
   return hipGetLastError();
 }
