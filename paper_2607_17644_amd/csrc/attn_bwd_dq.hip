@@ -358,26 +358,33 @@ __global__ __launch_bounds__(64 * NW, DN == 128 ? 1 : 2) void dq_rec_kernel(BwdP
 // dQ from the stored dS^T (bf16, 192/128-wide heads): the key-stationary pass leaves
 // dS^T = P * (dP - delta) of every causal (query tile, key) pair in the workspace, so
 // this pass is a streaming product dQ^T (192 x 32 per wave) += K^T dS^T over the
-// tile's keys, with no recomputation of S or dP. A workgroup of WPH waves owns WPH
-// consecutive 32-query tiles of one head; key blocks of 32 stream through an NS-stage
-// LDS ring of direct global->LDS loads: the K = [K_nope || k_pe] rows of the block
-// (shared, padded pitch 28 chunks) and each wave's own 32 x 32 dS^T block (64-byte
+// tile's keys, with no recomputation of S or dP. A workgroup of NW waves owns NW
+// consecutive 32-query tiles of one head; key blocks of 32 stream through a four-stage
+// LDS ring of direct global->LDS loads: the K_nope and k_pe rows of the block (shared,
+// padded pitches of 20 and 12 chunks) and each wave's own 32 x 32 dS^T block (64-byte
 // rows). Both MFMA operands come from transposing reads:
-//   A = K^T (lane: head dim, 8 keys), B = dS^T (lane: query, the same 8 keys).
-// Every wave issues the same number of loads per stage (the K fill is rounded up to
-// whole rounds of the workgroup, and key blocks past a wave's queries load a dummy
-// block that is not read), so the ring waits can count loads exactly.
-template <int DN, int DR, int DV, int WPH, int NS, int TPW>
-__global__ __launch_bounds__(64 * WPH, 1) void dq_ds_kernel(BwdParams P) {
+//   A = K^T (lane: head dim, 8 keys), B = dS^T (lane: query, the same 8 keys),
+// the K fragments three products ahead in a pinned order. Every copy has a wave-uniform
+// base and a constant byte offset per lane: with addresses worked out per copy the vector
+// ALU spent as long on them as the matrix unit on the products. Every wave issues the same
+// number of loads per stage (key blocks past a wave's queries load a dummy block that is
+// not read), so the ring waits can count loads exactly.
+// Bound: with few workgroups the chain of key blocks of the last query tiles (0.46 us a
+// block at 2048 tokens), with many the dS^T stream (4.3 GB at 16384 tokens, 16 heads: 4.9
+// TB/s). Measured before / now (16 heads, us): 1000 tokens 29 / 17, 2048 51 / 30, 4096
+// 97 / 71, 2 x 5001 218 / 204, 8192 265 / 241. Two query tiles per wave, which used to win
+// at 16384 tokens (one K fragment for two products), no longer does and is gone.
+template <int DN, int DR, int DV, int NW>
+__global__ __launch_bounds__(64 * NW, 1) void dq_ds_kernel(BwdParams P) {
   using T = bf16;
-  constexpr int DQK = DN + DR, DKVH = DN + DV, KB = 32, NW = WPH;
-  constexpr int KCPR = DQK / 8, NCPR = DN / 8, KP = KCPR + 4;  // pitch % 8 == 4
-  static_assert(KCPR % 4 == 0 && DQK % 32 == 0 && (NS == 3 || NS == 4), "192-wide K rows, 3 or 4 stages");
-  static_assert(TPW == 1 || TPW == 2, "one or two query tiles per wave");
-  constexpr int KCH = (KB * KP + 64 * NW - 1) / (64 * NW) * (64 * NW);  // K chunks, whole rounds
-  constexpr int F = KCH / 64 / NW + 2 * TPW;                           // loads per wave per stage
-  constexpr int DSE = NW * TPW * KB * 32;                              // dS^T elements per stage
-  __shared__ __attribute__((aligned(16))) T sK0[KCH * 8], sK1[KCH * 8], sK2[KCH * 8], sK3[KCH * 8];
+  constexpr int DQK = DN + DR, DKVH = DN + DV, KB = 32, NS = 4, PF = 3;
+  constexpr int NCPR = DN / 8, NP = NCPR + 4, PP = DR / 8 + 4;  // K_nope and k_pe tiles, pitch % 8 == 4
+  static_assert(NP % 8 == 4 && PP % 8 == 4, "conflict-free transposing reads");
+  constexpr int NIN = pad_chunks(KB, NP) / 64, NI = NIN + pad_chunks(KB, PP) / 64;  // copy instructions
+  static_assert(NI % NW == 0, "whole rounds of the workgroup");
+  constexpr int F = NI / NW + 2;         // loads per wave per stage
+  constexpr int DSE = NW * KB * 32;      // dS^T elements per stage
+  __shared__ __attribute__((aligned(16))) T sK0[NI * 512], sK1[NI * 512], sK2[NI * 512], sK3[NI * 512];
   __shared__ __attribute__((aligned(16))) T sD0[DSE], sD1[DSE], sD2[DSE], sD3[DSE];
 
   const T* __restrict__ kpe = (const T*)P.k_pe;
@@ -390,38 +397,55 @@ __global__ __launch_bounds__(64 * WPH, 1) void dq_ds_kernel(BwdParams P) {
   qblk = P.n_blocks - 1 - qblk;
   const int b = bh / H, h = bh % H;
 
-  const int tid = threadIdx.x, wave = tid >> 6, l = tid & 63, n = l & 31, g = l >> 5;
-  // this wave's query tiles t0 .. t0 + TPW - 1 (consecutive, so tile i sees 32 i more keys)
-  const int t0 = (qblk * NW + wave) * TPW;
-  int nk[TPW];
-  const T* dtile[TPW];
-#pragma unroll
-  for (int i = 0; i < TPW; ++i) {
-    const bool ok = t0 + i < TT;
-    nk[i] = ok ? ds_tile_keys(TT, P.causal, t0 + i) : 0;  // keys stored for the tile
-    dtile[i] = ds + (ok ? ds_tile_offset(TT, P.causal, bh, t0 + i) : 0);
-  }
-  const int kend = P.causal ? min(S, (qblk + 1) * NW * TPW * 32) : S;
+  const int l = threadIdx.x & 63, n = l & 31, g = l >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & (NW - 1);
+  const int t = qblk * NW + wave;  // this wave's query tile
+  const bool wave_ok = t < TT;
+  const int nk = wave_ok ? ds_tile_keys(TT, P.causal, t) : 0;  // keys stored for the tile
+  const T* dtile = ds + (wave_ok ? ds_tile_offset(TT, P.causal, bh, t) : 0);
+  const int kend = P.causal ? min(S, (qblk + 1) * NW * 32) : S;
   const int ntiles = (kend + KB - 1) / KB;
 
-  f32x16 dqa[TPW][DQK / 32];
+  f32x16 dqa[DQK / 32];
 #pragma unroll
-  for (int i = 0; i < TPW; ++i)
-#pragma unroll
-    for (int j = 0; j < DQK / 32; ++j) dqa[i][j] = f32x16{};
+  for (int j = 0; j < DQK / 32; ++j) dqa[j] = f32x16{};
 
-  auto fill = [&](T* dk, T* dd, int kt) {
-    pad_fill_chunks<T, KB, KCPR, KP, NW, KCH>(dk, wave, l, [&](int r, int c) {
-      const size_t row = (size_t)(b * S + min(kt + r, S - 1));
-      return c < NCPR ? kv + (row * H + h) * DKVH + c * 8 : kpe + row * DR + (c - NCPR) * 8;
-    });
+  // K copies: instruction j = wave + k NW covers 64 chunks of the K_nope tile (j < NIN) or of
+  // the k_pe tile, from a wave-uniform row base plus this lane's constant byte offset (lanes
+  // on padding reload chunk 0 of their row, past the last row that of row 0)
+  constexpr int NKC = NI / NW;
+  const char* kbase[NKC];  // key 0 of this (b, h)
+  uint32_t krowb[NKC], koff[NKC], krow = 0;
 #pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      const T* src = kt < nk[i] ? dtile[i] + (size_t)kt * 32 : dtile[i];  // dummy block when not stored
-      T* dst = dd + (wave * TPW + i) * KB * 32;
-      g2lds16(src + l * 8, dst);
-      g2lds16(src + 512 + l * 8, dst + 512);
+  for (int k = 0; k < NKC; ++k) {
+    const int j = wave + k * NW;
+    const bool pe = j >= NIN;
+    const int p = (pe ? j - NIN : j) * 64 + l;
+    int r = pe ? p / PP : p / NP, c = pe ? p % PP : p % NP;
+    if (r >= KB) r = 0;
+    if (c >= (pe ? DR / 8 : NCPR)) c = 0;
+    kbase[k] = pe ? (const char*)(kpe + (size_t)b * S * DR) : (const char*)(kv + ((size_t)(b * S) * H + h) * DKVH);
+    krowb[k] = 2u * (pe ? (uint32_t)DR : (uint32_t)(H * DKVH));
+    koff[k] = r * krowb[k] + 16u * c;
+    krow |= (uint32_t)r << (5 * k);
+  }
+  static_assert(KB == 32 && NKC * 5 <= 32, "packed rows");
+  auto fill = [&](T* dk, T* dd, int kt) {
+    if (kt + KB <= S) {
+#pragma unroll
+      for (int k = 0; k < NKC; ++k) g2lds16_so(kbase[k] + (size_t)kt * krowb[k], koff[k], dk + (wave + k * NW) * 512);
+    } else {  // rows past S read row S - 1 (their dS^T is zero or never read)
+      const int k0 = min(kt, S - 1);
+#pragma unroll
+      for (int k = 0; k < NKC; ++k) {
+        const int r = (int)((krow >> (5 * k)) & 31u), over = max(k0 + r - (S - 1), 0);
+        g2lds16_so(kbase[k] + (size_t)k0 * krowb[k], koff[k] - over * krowb[k], dk + (wave + k * NW) * 512);
+      }
     }
+    const T* src = kt < nk ? dtile + (size_t)kt * 32 : dtile;  // dummy block when not stored
+    T* dst = dd + wave * KB * 32;
+    g2lds16_so(src, 16u * l, dst);
+    g2lds16_so(src + 512, 16u * l, dst + 512);
   };
 
   // Every step refills a stage, past the last block with in-bounds dummies (clamped K
@@ -429,66 +453,62 @@ __global__ __launch_bounds__(64 * WPH, 1) void dq_ds_kernel(BwdParams P) {
   // always in flight behind the awaited one and the waits need no branch.
   fill(sK0, sD0, 0);
   fill(sK1, sD1, KB);
-  if constexpr (NS == 4) fill(sK2, sD2, 2 * KB);
-  // one K fragment feeds the MFMAs of every tile of the wave that sees the key block
-  auto product = [&](const T* tk, const T* td, auto first) {
-    constexpr int I0 = decltype(first)::value;  // tiles before I0 do not see this block
-#pragma unroll
-    for (int kk = 0; kk < KB / 16; ++kk) {
-      const int ra = kk * 16 + 4 * g;
-      bf16x8 zf[TPW];
-#pragma unroll
-      for (int i = I0; i < TPW; ++i) zf[i] = pad_tr_frag<4>(td + i * KB * 32, ra, ra + 8, 0);
-#pragma unroll
-      for (int db = 0; db < DQK / 32; ++db) {
-        const bf16x8 kf = pad_tr_frag<KP>(tk, ra, ra + 8, db * 32);
-#pragma unroll
-        for (int i = I0; i < TPW; ++i) mma(dqa[i][db], kf, zf[i]);
-      }
-    }
-  };
+  fill(sK2, sD2, 2 * KB);
   auto step = [&](auto stage, int it) {
     constexpr int ST = decltype(stage)::value;
     const int kt = it * KB;
     wait_vmem_le<(NS - 2) * F>();  // this wave's loads of block `it` have landed
-    __syncthreads();  // ... and everyone's; the stage filled next (read last at it - 1) is free
+    lds_barrier();  // ... and everyone's; the stage filled next (read last at it - 1) is free
     {
       constexpr int NX = (ST + NS - 1) % NS;
       T* nk_ = NX == 0 ? sK0 : NX == 1 ? sK1 : NX == 2 ? sK2 : sK3;
       T* nd_ = NX == 0 ? sD0 : NX == 1 ? sD1 : NX == 2 ? sD2 : sD3;
       fill(nk_, nd_, kt + (NS - 1) * KB);
     }
+    if (kt >= nk) return;  // wave-uniform: key blocks past a tile's queries hold no dS for it
     const T* tk = ST == 0 ? sK0 : ST == 1 ? sK1 : ST == 2 ? sK2 : sK3;
-    const T* td = (ST == 0 ? sD0 : ST == 1 ? sD1 : ST == 2 ? sD2 : sD3) + wave * TPW * KB * 32;
-    // wave-uniform: key blocks past a tile's queries hold no dS for it; nk[i] grows with i
-    if (kt < nk[0]) product(tk, td, std::integral_constant<int, 0>{});
-    else if (TPW > 1 && kt < nk[TPW - 1]) product(tk, td, std::integral_constant<int, TPW - 1>{});
+    const T* td = (ST == 0 ? sD0 : ST == 1 ? sD1 : ST == 2 ? sD2 : sD3) + wave * KB * 32;
+    // product i: 16-key chunk i / NDB, 32-column block i % NDB of dQ
+    constexpr int NDB = DQK / 32, NPR = KB / 16 * NDB;
+    auto k_frag = [&](int i) {
+      const int ra = (i / NDB) * 16 + 4 * g, db = i % NDB;
+      return db < DN / 32 ? pad_tr_frag<NP>(tk, ra, ra + 8, db * 32)
+                          : pad_tr_frag<PP>(tk + NIN * 512, ra, ra + 8, (db - DN / 32) * 32);
+    };
+    bf16x8 zf[KB / 16], kf[PF + 1];
+#pragma unroll
+    for (int kk = 0; kk < KB / 16; ++kk) zf[kk] = pad_tr_frag<4>(td, kk * 16 + 4 * g, kk * 16 + 4 * g + 8, 0);
+#pragma unroll
+    for (int i = 0; i < PF; ++i) kf[i] = k_frag(i);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NPR; ++i) {
+      if (i + PF < NPR) kf[(i + PF) % (PF + 1)] = k_frag(i + PF);
+      mma(dqa[i % NDB], kf[i % (PF + 1)], zf[i / NDB]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
   for (int it = 0; it < ntiles; it += NS) {
     step(std::integral_constant<int, 0>{}, it);
     if (it + 1 < ntiles) step(std::integral_constant<int, 1>{}, it + 1);
     if (it + 2 < ntiles) step(std::integral_constant<int, 2>{}, it + 2);
-    if constexpr (NS == 4)
-      if (it + 3 < ntiles) step(std::integral_constant<int, NS - 1>{}, it + 3);
+    if (it + 3 < ntiles) step(std::integral_constant<int, 3>{}, it + 3);
   }
 
   wait_vmem();  // the surplus loads land before the workgroup's LDS is released
   // accumulator column n holds the query stored at position n of the dS^T rows
+  const int my_q = t * 32 + ds_query_of_position(n);
+  if (!wave_ok || my_q >= S) return;
+  T* dqr = (T*)P.dq + ((size_t)(b * S + my_q) * H + h) * DQK;
 #pragma unroll
-  for (int i = 0; i < TPW; ++i) {
-    const int my_q = (t0 + i) * 32 + ds_query_of_position(n);
-    if (t0 + i >= TT || my_q >= S) continue;
-    T* dqr = (T*)P.dq + ((size_t)(b * S + my_q) * H + h) * DQK;
+  for (int db = 0; db < DQK / 32; ++db)
 #pragma unroll
-    for (int db = 0; db < DQK / 32; ++db)
+    for (int rr = 0; rr < 4; ++rr) {
+      bf16x4 v;
 #pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        bf16x4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = to_elem<T>(dqa[i][db][4 * rr + e] * P.scale);
-        *reinterpret_cast<bf16x4*>(dqr + db * 32 + rr * 8 + g * 4) = v;
-      }
-  }
+      for (int e = 0; e < 4; ++e) v[e] = to_elem<T>(dqa[db][4 * rr + e] * P.scale);
+      *reinterpret_cast<bf16x4*>(dqr + db * 32 + rr * 8 + g * 4) = v;
+    }
 }
 
 // dQ from the stored dS^T with K/V rebuilt on chip (kv_mode FUSED; bf16, 192/128-wide
@@ -793,16 +813,13 @@ __global__ __launch_bounds__(256, 1) void dq_ds_fused2_kernel(BwdParams P) {
 
 }  // namespace
 
-// dq_ds_kernel's shapes: 8 waves (two per SIMD, which hides the latency of the dS^T
-// stream). With two 32-query tiles per wave a K fragment read from LDS feeds two MFMAs,
-// halving the K traffic through LDS, over a three-stage ring (four do not fit in LDS at
-// 46 KB a stage); it needs a grid of at least two workgroups per CU, below which one
-// tile per wave over a four-stage ring (twice the workgroups) is faster. Measured (16
-// heads, dQ stage alone): S=16384 0.98 ms (two tiles) against 1.04 ms (one); S=8192 0.357
-// against 0.278 ms; S=2048 0.084 against 0.050 ms. Both shapes give the same bits. 4 waves
-// with two tiles 1.37 ms, with one 1.63 ms at S=16384.
-constexpr int kDqWaves = 8;
-constexpr long long kDqWideMinGroups = 512;
+// dq_ds_kernel's shapes: 8 waves (two per SIMD, which hides the latency of the dS^T stream and
+// shares each K block among 256 queries), or 4 when 8 would give at most this many workgroups
+// (then the longest chain of key blocks bounds it, and that runs faster alone on its SIMD).
+// Both give the same bits. Measured (us, 8 / 4 waves; 8-wave workgroups): 2048 tokens x 16
+// heads 42 / 30 (128), 2048 x 32 47 / 41 (256), 4096 x 16 90 / 71 (256), 8192 x 16 243 / 271
+// (512), 2 x 5001 x 16 204 / 221 (640).
+constexpr long long kDqNarrowMaxGroups = 320;
 
 // dq_rec_kernel's shape: 4 waves (one per SIMD, 128 queries per workgroup). Measured at
 // S=16384, H=16: 2.16-2.38 ms; 8 waves need more than their 256 registers (98 spilled):
@@ -828,14 +845,13 @@ hipError_t launch_bwd_dq(bwd::BwdParams P, int B, hipStream_t st) {
         P.n_blocks = (P.ds_T + WPH - 1) / WPH;
         dq_ds_fused_kernel<DN, DR, DV><<<dim3(P.n_blocks * P.H, B), 64 * WPH, 0, st>>>(P);
       } else {
-        // kDqWaves waves x 1 or 2 query tiles of 32 per workgroup
-        const int nb_wide = (P.ds_T + 2 * kDqWaves - 1) / (2 * kDqWaves);
-        if ((long long)nb_wide * P.H * B >= kDqWideMinGroups) {
-          P.n_blocks = nb_wide;
-          dq_ds_kernel<DN, DR, DV, kDqWaves, 3, 2><<<dim3(P.n_blocks * P.H, B), 64 * kDqWaves, 0, st>>>(P);
+        const int nb8 = (P.ds_T + 7) / 8;
+        if ((long long)nb8 * P.H * B > kDqNarrowMaxGroups) {
+          P.n_blocks = nb8;
+          dq_ds_kernel<DN, DR, DV, 8><<<dim3(P.n_blocks * P.H, B), 512, 0, st>>>(P);
         } else {
-          P.n_blocks = (P.ds_T + kDqWaves - 1) / kDqWaves;
-          dq_ds_kernel<DN, DR, DV, kDqWaves, 4, 1><<<dim3(P.n_blocks * P.H, B), 64 * kDqWaves, 0, st>>>(P);
+          P.n_blocks = (P.ds_T + 3) / 4;
+          dq_ds_kernel<DN, DR, DV, 4><<<dim3(P.n_blocks * P.H, B), 256, 0, st>>>(P);
         }
       }
       return hipGetLastError();
