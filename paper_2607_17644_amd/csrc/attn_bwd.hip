@@ -110,6 +110,10 @@ __global__ __launch_bounds__(256) void delta_kernel(const T* __restrict__ out, c
 // the four slots and every LDS read is a per-lane base register plus an immediate
 // offset, with no address arithmetic in the loop. The per-wave issue rate, not the LDS,
 // is then its limit. It also stores dZ (bf16) as dS^T for the dQ pass.
+// With QS = 2 (short sequences, see kDkdvSplitMaxCausal) a workgroup owns 64 keys and takes
+// two query tiles per step: waves 0, 1 the even ones, waves 2, 3 the odd ones of the same
+// keys, over a three-slot ring (three slots of two tiles fill the LDS); the two partial sums
+// meet in LDS at the end.
 // Low part of an accumulator half rounded to bf16: bf16(x - float(hi)) for the 8 values
 // that acc_to_frag turned into `hi`, so that hi + lo carries about 16 significant bits
 // (x - float(hi) is exact in fp32).
@@ -121,23 +125,36 @@ __device__ __forceinline__ bf16x8 acc_lo_frag(const f32x16& acc, int half, const
   return __builtin_convertvector(v, bf16x8);
 }
 
-template <int DN, int DR, int DV, bool STORE_DS, bool FUSED>
+// The same with x rounded to fp32 first, whatever surrounds it: left to contraction, x = p * d
+// and the subtraction become one fused operation in some variants of the kernel and not in
+// others, and their dk_pe would differ in the last bits.
+__device__ __forceinline__ bf16x8 acc_lo_frag_rounded(const f32x16& acc, int half, const bf16x8& hi) {
+#pragma clang fp contract(off)
+  typedef float f32x8v __attribute__((ext_vector_type(8)));
+  f32x8v v;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = acc[8 * half + e] - (float)hi[e];
+  return __builtin_convertvector(v, bf16x8);
+}
+
+template <int DN, int DR, int DV, bool STORE_DS, bool FUSED, int QS>
 __global__ __launch_bounds__(256, 1) void dkdv32_kernel(BwdParams P) {
   using T = bf16;
-  constexpr int DQK = DN + DR, DKVH = DN + DV, NW = 4, BK = 32 * NW, BQ = 32, NS = 4;
+  static_assert(QS == 1 || QS == 2, "query tiles per step");
+  constexpr int DQK = DN + DR, DKVH = DN + DV, NW = 4, KW = NW / QS, BK = 32 * KW, BQ = 32, NS = QS == 1 ? 4 : 3;
   constexpr int QCPR = DQK / 8, OCPR = DV / 8;
   static_assert(QCPR == 24 && OCPR == 16, "swizzles are defined for 192/128-wide rows");
   constexpr int QCH = BQ * QCPR, OCH = BQ * OCPR;
   constexpr int KQ = QCH / 64 / NW, KO = OCH / 64 / NW;
   static_assert(KQ * 64 * NW == QCH && KO * 64 * NW == OCH && 5 * (KQ + KO) <= 32, "load split");
   constexpr int F = KQ + KO + 1;
-  constexpr int QTB = QCH * 16, OTB = OCH * 16;  // tile bytes
+  constexpr int QTB = QCH * 16 * QS, OTB = OCH * 16 * QS;  // slot bytes
   // dK^T blocks RB, RB + 1 are the rope band [DN, DN + DR): their product takes dZ as a bf16
   // pair hi + lo, because dk_pe sums that band over every head and every query
   constexpr int RB = DN / 32;
   static_assert(DR == 64 && RB + 2 == DQK / 32, "two 32-wide rope blocks at the end of dK^T");
-  __shared__ __attribute__((aligned(16))) T sQ[NS][QCH * 8];
-  __shared__ __attribute__((aligned(16))) T sO[NS][OCH * 8];
+  __shared__ __attribute__((aligned(16))) T sQ[NS][QCH * 8 * QS];
+  __shared__ __attribute__((aligned(16))) T sO[NS][OCH * 8 * QS];
   __shared__ __attribute__((aligned(16))) float sL[NS][NW][256];
 
   const T* __restrict__ q = (const T*)P.q;
@@ -152,7 +169,8 @@ __global__ __launch_bounds__(256, 1) void dkdv32_kernel(BwdParams P) {
 
   const int tid = threadIdx.x, l = tid & 63, n = l & 31, g = l >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) & (NW - 1);
-  const int k0 = kb * BK + wave * 32;
+  const int kw = QS == 1 ? wave : wave % KW, qw = QS == 1 ? 0 : wave / KW;
+  const int k0 = kb * BK + kw * 32;
   const int my_k = k0 + n;
   const bool key_ok = my_k < S;
   const size_t krow = (size_t)(b * S + (key_ok ? my_k : 0));
@@ -160,7 +178,7 @@ __global__ __launch_bounds__(256, 1) void dkdv32_kernel(BwdParams P) {
   const unsigned q_span = key_ok ? (unsigned)(S - q_lo) : 0u;
 
   const int qt_begin = P.causal ? kb * BK : 0;
-  const int ntiles = (S - qt_begin + BQ - 1) / BQ;
+  const int ntiles = (S - qt_begin + BQ * QS - 1) / (BQ * QS);  // steps
 
   const size_t hrow0 = (size_t)(b * S) * H + h;
   uint32_t qoff[KQ], ooff[KO], rows = 0;
@@ -178,6 +196,37 @@ __global__ __launch_bounds__(256, 1) void dkdv32_kernel(BwdParams P) {
   }
   const float* llane = ((l & 15) < 8 ? P.lse2 : P.delta) + (size_t)bh * P.S_pad + 4 * (l & 7);
   auto fill = [&](int st, int qt) {
+    if constexpr (QS > 1) {
+      // QS consecutive tiles (a row's swizzle and lane offset do not depend on its tile);
+      // rows past S read row S - 1, tiles past S too
+#pragma unroll
+      for (int i = 0; i < QS; ++i) {
+        const int t0 = min(qt + i * BQ, S - 1), rmax = S - 1 - t0;
+        const T* qb = q + (hrow0 + (size_t)t0 * H) * DQK;
+        const T* ob = dout + (hrow0 + (size_t)t0 * H) * DV;
+        T* dq = &sQ[st][i * QCH * 8];
+        T* dO = &sO[st][i * OCH * 8];
+        if (rmax >= BQ - 1) {
+#pragma unroll
+          for (int k = 0; k < KQ; ++k) g2lds16_so(qb, qoff[k], dq + (wave + k * NW) * 512);
+#pragma unroll
+          for (int k = 0; k < KO; ++k) g2lds16_so(ob, ooff[k], dO + (wave + k * NW) * 512);
+        } else {
+#pragma unroll
+          for (int k = 0; k < KQ; ++k) {
+            const int over = max((int)((rows >> (5 * k)) & 31u) - rmax, 0);
+            g2lds16_so(qb, qoff[k] - 2u * over * H * DQK, dq + (wave + k * NW) * 512);
+          }
+#pragma unroll
+          for (int k = 0; k < KO; ++k) {
+            const int over = max((int)((rows >> (5 * (KQ + k))) & 31u) - rmax, 0);
+            g2lds16_so(ob, ooff[k] - 2u * over * H * DV, dO + (wave + k * NW) * 512);
+          }
+        }
+      }
+      g2lds16(llane + qt + qw * BQ, sL[st][wave]);  // this wave's tile (rows padded to kRowPad = QS * BQ)
+      return;
+    }
     const T* qb = q + (hrow0 + (size_t)qt * H) * DQK;
     const T* ob = dout + (hrow0 + (size_t)qt * H) * DV;
     if (qt + BQ <= S) {
@@ -276,6 +325,7 @@ __global__ __launch_bounds__(256, 1) void dkdv32_kernel(BwdParams P) {
   typedef __attribute__((address_space(3))) const char* lptr;
   typedef __attribute__((address_space(3))) const frag_t<T> lfrag;
   typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+  const uint32_t q_tile = QS == 1 ? 0u : qw * (QTB / QS), o_tile = QS == 1 ? 0u : qw * (OTB / QS);
   auto base = [](const void* arr, uint32_t off) {
     lptr p = (lptr)(const char*)arr + off;
     asm volatile("" : "+v"(p));
@@ -287,18 +337,18 @@ __global__ __launch_bounds__(256, 1) void dkdv32_kernel(BwdParams P) {
     const int lc = 2 * ((l >> 4) & 1) + ((s16 & 3) >> 1), e4 = 4 * (s16 & 1);
     const int sq = swz<QCPR>(n), so = swz<OCPR>(n);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) Qr[j] = base(sQ, 2u * (n * DQK + ((2 * j + g) ^ sq) * 8));
+    for (int j = 0; j < 4; ++j) Qr[j] = base(sQ, q_tile + 2u * (n * DQK + ((2 * j + g) ^ sq) * 8));
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      Qa[j] = base(sQ, 2u * (ra * DQK + ((4 * j + lc) ^ swz<QCPR>(ra)) * 8 + e4));
-      Qbo[j] = base(sQ, 2u * (rb * DQK + ((4 * j + lc) ^ swz<QCPR>(rb)) * 8 + e4));
+      Qa[j] = base(sQ, q_tile + 2u * (ra * DQK + ((4 * j + lc) ^ swz<QCPR>(ra)) * 8 + e4));
+      Qbo[j] = base(sQ, q_tile + 2u * (rb * DQK + ((4 * j + lc) ^ swz<QCPR>(rb)) * 8 + e4));
     }
 #pragma unroll
-    for (int ks = 0; ks < DV / 16; ++ks) Or[ks] = base(sO, 2u * (n * DV + ((2 * ks + g) ^ so) * 8));
+    for (int ks = 0; ks < DV / 16; ++ks) Or[ks] = base(sO, o_tile + 2u * (n * DV + ((2 * ks + g) ^ so) * 8));
 #pragma unroll
     for (int db = 0; db < DV / 32; ++db) {
-      Oa[db] = base(sO, 2u * (ra * DV + ((4 * db + lc) ^ swz<OCPR>(ra)) * 8 + e4));
-      Obo[db] = base(sO, 2u * (rb * DV + ((4 * db + lc) ^ swz<OCPR>(rb)) * 8 + e4));
+      Oa[db] = base(sO, o_tile + 2u * (ra * DV + ((4 * db + lc) ^ swz<OCPR>(ra)) * 8 + e4));
+      Obo[db] = base(sO, o_tile + 2u * (rb * DV + ((4 * db + lc) ^ swz<OCPR>(rb)) * 8 + e4));
     }
   }
   auto tr = [](lptr pa, lptr pb) {
@@ -328,7 +378,7 @@ __global__ __launch_bounds__(256, 1) void dkdv32_kernel(BwdParams P) {
     }
   };
   auto mask_b = [&](int j, f32x16& sa) {
-    const int qt = qt_begin + j * BQ;
+    const int qt = qt_begin + (j * QS + qw) * BQ;
     if ((P.causal && qt < k0 + 31) || qt + BQ > S || k0 + 32 > S) {
       asm volatile("");
 #pragma unroll
@@ -355,14 +405,14 @@ __global__ __launch_bounds__(256, 1) void dkdv32_kernel(BwdParams P) {
     for (int kk = 0; kk < BQ / 16; ++kk) {
       pf[kk] = acc_to_frag<T>(p, kk);
       zf[kk] = acc_to_frag<T>(z, kk);
-      if constexpr (HILO) zl[kk] = acc_lo_frag(z, kk, zf[kk]);
+      if constexpr (HILO) zl[kk] = QS > 1 ? acc_lo_frag_rounded(z, kk, zf[kk]) : acc_lo_frag(z, kk, zf[kk]);
     }
   };
   T* const dsw = STORE_DS ? (T*)P.ds + ds_tile_offset(P.ds_T, P.causal, bh, 0) + (size_t)k0 * BQ : nullptr;
   auto store_ds = [&](int j, const bf16x8 (&zf)[2]) {
     if constexpr (!STORE_DS) return;
-    const int t = (qt_begin + j * BQ) / BQ;
-    if (my_k < ds_tile_keys(P.ds_T, P.causal, t)) {
+    const int t = (qt_begin + (j * QS + qw) * BQ) / BQ;
+    if ((QS == 1 || t < P.ds_T) && my_k < ds_tile_keys(P.ds_T, P.causal, t)) {
       // accumulator element r of this lane is query 8 (r / 4) + 4 g + r % 4: position 16 g + r.
       // Non-temporal: the store is read back only by the dQ pass, long after this kernel.
       T* dsr = dsw + (P.causal ? (size_t)512 * t * (t + 1) : (size_t)1024 * P.ds_T * t) + (n * BQ + g * 16);
@@ -374,11 +424,20 @@ __global__ __launch_bounds__(256, 1) void dkdv32_kernel(BwdParams P) {
   // Every tile step refills a slot, past the end with another copy of the last tile (a
   // slot nobody reads any more), so one tile of copies is always in flight behind the
   // awaited one and the wait needs no branch.
-  auto tile_q = [&](int j) { return qt_begin + min(j, ntiles - 1) * BQ; };
+  auto tile_q = [&](int j) { return qt_begin + min(j, ntiles - 1) * (BQ * QS); };
   auto sync = [&](int j) {
-    wait_vmem_le<F>();
-    lds_barrier();
-    fill((j + 2) % NS, tile_q(j + 2));
+    if constexpr (QS == 1) {
+      wait_vmem_le<F>();
+      lds_barrier();
+      fill((j + 2) % NS, tile_q(j + 2));
+    } else {  // three slots hold the tiles of this step, the previous and the next one
+      // younger than the awaited copies are only the two dS^T stores of step j - 1 (a wave may
+      // have none there on the diagonal, j = 1 and 2: then everything is awaited)
+      if (STORE_DS && j > 2) wait_vmem_le<2>();
+      else wait_vmem();
+      lds_barrier();
+      fill((j + 1) % NS, tile_q(j + 1));
+    }
   };
 
   // The sweep over the query tiles, compiled twice: with HILO the rope band of dK^T takes
@@ -386,16 +445,17 @@ __global__ __launch_bounds__(256, 1) void dkdv32_kernel(BwdParams P) {
   auto sweep = [&](auto hc) {
   constexpr bool HILO = decltype(hc)::value;
   fill(0, qt_begin);
-  fill(1, tile_q(1));
+  if constexpr (QS == 1) fill(1, tile_q(1));
   f32x16 sa0, dp0, sa1, dp1;
   bf16x8 pf[2], zf[2], zl[2];
   sync(0);
   step_a(0, sa0, dp0);
   constexpr int PF = 3;
-  // step of tile jj (slot K = jj % 4): B(jj - 1) beside A(jj), then C(jj - 1)
+  // step of tile jj (K = jj modulo the unrolling, slot jj % NS): B(jj - 1) beside A(jj), then
+  // C(jj - 1)
   auto step = [&](auto kc, int jj) {
     constexpr int K = decltype(kc)::value;
-    constexpr int ST = K, SP = (K + NS - 1) % NS, ODD = K & 1;
+    constexpr int ST = K % NS, SP = (K + NS - 1) % NS, ODD = K & 1;
     f32x16& sa_a = ODD ? sa1 : sa0;
     f32x16& dp_a = ODD ? dp1 : dp0;
     f32x16& sa_b = ODD ? sa0 : sa1;
@@ -435,8 +495,9 @@ __global__ __launch_bounds__(256, 1) void dkdv32_kernel(BwdParams P) {
     for (int kk = 0; kk < BQ / 16; ++kk) {
       pf[kk] = acc_to_frag<T>(p, kk);
       zf[kk] = acc_to_frag<T>(z, kk);
-      if constexpr (HILO) zl[kk] = acc_lo_frag(z, kk, zf[kk]);
+      if constexpr (HILO) zl[kk] = QS > 1 ? acc_lo_frag_rounded(z, kk, zf[kk]) : acc_lo_frag(z, kk, zf[kk]);
     }
+    if constexpr (QS > 1) store_ds(jj - 1, zf);  // lands behind C: the next wait covers it
     bf16x8 cb[PF + 1], c_r0, c_r1;
 #pragma unroll
     for (int i = 0; i < PF; ++i) cb[i] = c_read(SP, i);
@@ -459,13 +520,30 @@ __global__ __launch_bounds__(256, 1) void dkdv32_kernel(BwdParams P) {
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    store_ds(jj - 1, zf);
+    if constexpr (QS == 1) store_ds(jj - 1, zf);
   };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
   using I2 = std::integral_constant<int, 2>;
   using I3 = std::integral_constant<int, 3>;
-  {
+  if constexpr (QS > 1) {  // slots repeat every three steps, accumulator sets every two
+    using I4 = std::integral_constant<int, 4>;
+    using I5 = std::integral_constant<int, 5>;
+    int j = 1;
+    for (; j + 5 < ntiles; j += 6) {
+      step(I1{}, j);
+      step(I2{}, j + 1);
+      step(I3{}, j + 2);
+      step(I4{}, j + 3);
+      step(I5{}, j + 4);
+      step(I0{}, j + 5);
+    }
+    if (j < ntiles) step(I1{}, j++);
+    if (j < ntiles) step(I2{}, j++);
+    if (j < ntiles) step(I3{}, j++);
+    if (j < ntiles) step(I4{}, j++);
+    if (j < ntiles) step(I5{}, j++);
+  } else {
     int j = 1;
     for (; j + 3 < ntiles; j += 4) {
       step(I1{}, j);
@@ -498,45 +576,114 @@ __global__ __launch_bounds__(256, 1) void dkdv32_kernel(BwdParams P) {
     store_ds(jl, zf);
   }
   };
-  if (kb == 0) sweep(std::true_type{});
+  if (kb < QS) sweep(std::true_type{});  // keys 0 .. 127
   else sweep(std::false_type{});
   wait_vmem();  // the surplus copies land before the workgroup's LDS is released
 
-  if (!key_ok) return;
-  const size_t row = krow * H + h;
-  T* dkvr = (T*)P.dkv + row * DKVH;
-  T* dkvl = (T*)P.dkv_lo + row * DKVH;
-  float* dper = P.dkpe_h + row * DR;
-  auto put = [&](int col, const f32x4& v) {
-    bf16x4 hi, lo;
+  // Two waves hold partial sums of the same keys, over the even and the odd query tiles: the
+  // first takes the second's dK and finishes it, the second takes the first's dV (even + odd).
+  if constexpr (QS > 1) {
+    lds_barrier();  // every wave's reads of the ring, and copies into it, are done
+    float* xk = (float*)&sQ[0][0] + kw * (DQK / 32 * 1024) + l * 4;
+    float* xv = (float*)&sO[0][0] + kw * (DV / 32 * 1024) + l * 4;
+    static_assert(KW * DQK / 32 * 4096 <= NS * QTB && KW * DV / 32 * 4096 <= NS * OTB, "partials fit the ring");
+    auto put_x = [](float* x, const f32x16& a) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      hi[e] = to_elem<T>(v[e]);
-      lo[e] = to_elem<T>(v[e] - to_f32(hi[e]));
+      for (int r = 0; r < 4; ++r) *reinterpret_cast<f32x4*>(x + r * 256) = f32x4{a[4 * r], a[4 * r + 1], a[4 * r + 2], a[4 * r + 3]};
+    };
+    auto add_x = [](const float* x, f32x16& a) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(x + r * 256);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[4 * r + e] += v[e];
+      }
+    };
+    if (qw == 0) {
+#pragma unroll
+      for (int i = 0; i < DV / 32; ++i) put_x(xv + i * 1024, dv[i]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < DQK / 32; ++i) put_x(xk + i * 1024, dk[i]);
     }
-    *reinterpret_cast<bf16x4*>(dkvr + col) = hi;
-    *reinterpret_cast<bf16x4*>(dkvl + col) = lo;
+    lds_barrier();
+    if (qw == 0) {
+#pragma unroll
+      for (int i = 0; i < DQK / 32; ++i) add_x(xk + i * 1024, dk[i]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < DV / 32; ++i) add_x(xv + i * 1024, dv[i]);
+    }
+  }
+
+  // Results leave through LDS in rows: in the accumulators a lane holds 4 consecutive columns
+  // of one key, so stores straight from them would write 16 bytes into each of 32 rows 8 KB
+  // apart per instruction (80 such instructions per wave took as long as five tiles). Each
+  // wave stages 32 keys x 256 bytes in 8 KB of its own (16-byte chunk c of row n at
+  // c ^ (n & 15)) and stores whole 256-byte rows.
+  lds_barrier();  // every wave's reads of the ring are done
+  char* const xh = (char*)&sQ[0][0] + wave * 8192;
+  char* const xl = (char*)&sO[0][0] + wave * 8192;
+  static_assert(NW * 8192 <= NS * QTB && NW * 8192 <= NS * OTB, "staging fits the ring");
+  const int kr0 = k0 + (l >> 4);  // this lane's key of the first stored row group
+  const uint32_t xo = n * 256, xr = (l >> 4) * 256;
+  auto sync_wave = [] {  // a wave's LDS accesses complete in order; keep the compiler's order too
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   };
+  // columns [col0, col0 + 128) of dKV (times mul) as bf16 hi and lo rows
+  auto put_dkv = [&](const f32x16* acc, float mul, int col0) {
 #pragma unroll
-  for (int db = 0; db < DQK / 32; ++db)
+    for (int db = 0; db < 4; ++db)
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      const int d = db * 32 + rr * 8 + g * 4;
-      f32x4 v;
+      for (int rr = 0; rr < 4; ++rr) {
+        bf16x4 hi, lo;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = dk[db][4 * rr + e] * P.scale;
-      if (d >= DN) *reinterpret_cast<f32x4*>(dper + (d - DN)) = v;
-      else put(d, v);
+        for (int e = 0; e < 4; ++e) {
+          const float v = acc[db][4 * rr + e] * mul;
+          hi[e] = to_elem<T>(v);
+          lo[e] = to_elem<T>(v - to_f32(hi[e]));
+        }
+        const uint32_t o = xo + (((db * 4 + rr) ^ (n & 15)) << 4) + g * 8;
+        *reinterpret_cast<bf16x4*>(xh + o) = hi;
+        *reinterpret_cast<bf16x4*>(xl + o) = lo;
+      }
+    sync_wave();
+    const size_t o0 = ((size_t)(b * S + kr0) * H + h) * DKVH + col0 + (l & 15) * 8;
+#pragma unroll
+    for (int it = 0; it < 8; ++it) {  // rows 4 it + l / 16, chunk l % 16
+      if (kr0 + 4 * it < S) {
+        const uint32_t o = xr + it * 1024 + (((l & 15) ^ ((4 * it + (l >> 4)) & 15)) << 4);
+        const size_t d = o0 + (size_t)(4 * it) * H * DKVH;
+        *reinterpret_cast<chunk16*>((T*)P.dkv + d) = *reinterpret_cast<const chunk16*>(xh + o);
+        *reinterpret_cast<chunk16*>((T*)P.dkv_lo + d) = *reinterpret_cast<const chunk16*>(xl + o);
+      }
     }
+    sync_wave();
+  };
+  static_assert(DN == 128 && DV == 128 && DR == 64, "256-byte rows of each");
+  if (QS == 1 || qw == 0) {
+    put_dkv(dk, P.scale, 0);
+    // the rope band of dK (fp32, per head)
 #pragma unroll
-  for (int db = 0; db < DV / 32; ++db)
+    for (int db = 0; db < 2; ++db)
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      f32x4 v;
+      for (int rr = 0; rr < 4; ++rr) {
+        f32x4 v;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = dv[db][4 * rr + e];
-      put(DN + db * 32 + rr * 8 + g * 4, v);
-    }
+        for (int e = 0; e < 4; ++e) v[e] = dk[RB + db][4 * rr + e] * P.scale;
+        *reinterpret_cast<f32x4*>(xh + xo + (((db * 8 + rr * 2 + g) ^ (n & 15)) << 4)) = v;
+      }
+    sync_wave();
+    float* dper = P.dkpe_h + ((size_t)(b * S + kr0) * H + h) * DR + (l & 15) * 4;
+#pragma unroll
+    for (int it = 0; it < 8; ++it)
+      if (kr0 + 4 * it < S)
+        *reinterpret_cast<f32x4*>(dper + (size_t)(4 * it) * H * DR) = *reinterpret_cast<const f32x4*>(
+            xh + xr + it * 1024 + (((l & 15) ^ ((4 * it + (l >> 4)) & 15)) << 4));
+    sync_wave();
+  }
+  if (QS == 1 || qw == 1) put_dkv(dv, 1.f, DN);
 }
 
 
@@ -555,6 +702,32 @@ __global__ __launch_bounds__(256) void dkpe_kernel(const float* __restrict__ par
 
 }  // namespace
 
+#ifndef LAGA_SHORT_SEQ
+namespace {
+constexpr int kQS = 1;
+}
+hipError_t launch_dkdv32(BwdParams P, int B, hipStream_t st) {
+  if (P.S < (P.causal ? kDkdvSplitMaxCausal : kDkdvSplitMaxFull)) return launch_dkdv32_short(P, B, st);
+#else
+namespace {
+constexpr int kQS = 2;
+}
+hipError_t launch_dkdv32_short(BwdParams P, int B, hipStream_t st) {
+#endif
+  constexpr int BK = 128 / kQS;
+  P.n_blocks = (P.S + BK - 1) / BK;
+  const dim3 grid(P.n_blocks * P.H, B);
+  if (P.w_t) {
+    if (P.ds) dkdv32_kernel<128, 64, 128, true, true, kQS><<<grid, 256, 0, st>>>(P);
+    else dkdv32_kernel<128, 64, 128, false, true, kQS><<<grid, 256, 0, st>>>(P);
+  } else {
+    if (P.ds) dkdv32_kernel<128, 64, 128, true, false, kQS><<<grid, 256, 0, st>>>(P);
+    else dkdv32_kernel<128, 64, 128, false, false, kQS><<<grid, 256, 0, st>>>(P);
+  }
+  return hipGetLastError();
+}
+
+#ifndef LAGA_SHORT_SEQ
 template <typename T, int DN, int DR, int DV>
 hipError_t launch_attn_bwd(const AttnBwdArgs& a, int stage, hipStream_t st) {
   using Tl = BwdTiles<T>;
@@ -571,15 +744,7 @@ hipError_t launch_attn_bwd(const AttnBwdArgs& a, int stage, hipStream_t st) {
                                                       a.S, a.S_pad, a.H, BS);
   } else if (stage == 1) {
     if constexpr (sizeof(T) == 2 && DN + DR == 192 && DV == 128) {
-      P.n_blocks = (a.S + 127) / 128;
-      const dim3 grid(P.n_blocks * a.H, a.B);
-      if (a.w_t) {
-        if (a.ds) dkdv32_kernel<DN, DR, DV, true, true><<<grid, 256, 0, st>>>(P);
-        else dkdv32_kernel<DN, DR, DV, false, true><<<grid, 256, 0, st>>>(P);
-      } else {
-        if (a.ds) dkdv32_kernel<DN, DR, DV, true, false><<<grid, 256, 0, st>>>(P);
-        else dkdv32_kernel<DN, DR, DV, false, false><<<grid, 256, 0, st>>>(P);
-      }
+      return launch_dkdv32(P, a.B, st);
     } else if constexpr (sizeof(T) == 2 && DN == 64) {
       return launch_dkdv_half(P, a.B, st);
     } else {
@@ -601,5 +766,6 @@ LAGA_INST_BWD(bf16, 32, 16, 32)
 LAGA_INST_BWD(float, 32, 16, 32)
 LAGA_INST_BWD(bf16, 64, 32, 64)
 LAGA_INST_BWD(float, 64, 32, 64)
+#endif
 
 }  // namespace laga

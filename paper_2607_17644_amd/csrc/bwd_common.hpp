@@ -65,6 +65,17 @@ __host__ __device__ inline size_t ds_tile_offset(int T, int causal, int bh, int 
 }
 __host__ __device__ inline int ds_tile_keys(int T, int causal, int t) { return causal ? 32 * (t + 1) : 32 * T; }
 
+// Sequence lengths below which dK/dV splits the queries over pairs of waves (dkdv32_kernel with
+// QS = 2; causal, full). A function of the sequence length and the mask alone, so that a
+// head's gradients do not depend on the heads or batch elements beside it; the lines are set
+// for the rank's share of 16 heads. A workgroup's first keys see every query, so with few
+// workgroups that chain is the kernel's time, and the split halves it; but its step takes
+// 13 % longer (copies one step ahead instead of two) and twice the workgroups pay 10 us of
+// first loads and last stores. Measured (us, QS = 1 / 2): 16 heads, causal: 300 tokens 22 /
+// 17, 1000 51 / 35, 2048 90 / 73, 3000 141 / 141; 32 heads: 1000 54 / 48, 2048 124 / 137; 64
+// heads: 1000 74 / 90. 16 heads, no mask: 1000 51 / 38, 1900 105 / 112.
+constexpr int kDkdvSplitMaxCausal = 2304, kDkdvSplitMaxFull = 1280;
+
 template <typename T> struct BwdTiles;
 template <> struct BwdTiles<bf16> { static constexpr int BQ = 32, BC = 64, WPH_KV = 4, WPH_Q = 4; };
 template <> struct BwdTiles<float> { static constexpr int BQ = 32, BC = 32, WPH_KV = 4, WPH_Q = 4; };

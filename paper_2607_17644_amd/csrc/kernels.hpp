@@ -107,6 +107,10 @@ struct AttnBwdArgs {
 namespace bwd { struct BwdParams; }
 template <typename T, int DN, int DR, int DV>
 hipError_t launch_bwd_dq(bwd::BwdParams P, int B, hipStream_t st);
+// the key-stationary dK/dV pass for bf16 with 192/128-wide heads: the rule between the two
+// (attn_bwd.hip), and the one for short sequences (attn_bwd_short.hip)
+hipError_t launch_dkdv32(bwd::BwdParams P, int B, hipStream_t st);
+hipError_t launch_dkdv32_short(bwd::BwdParams P, int B, hipStream_t st);
 // the generic key-stationary dK/dV kernel (attn_bwd_kv.hip)
 template <typename T, int DN, int DR, int DV>
 hipError_t launch_dkdv_generic(bwd::BwdParams P, int B, hipStream_t st);
