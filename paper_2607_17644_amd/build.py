@@ -19,7 +19,7 @@ BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "liblaga.so")
 ARCH = "gfx950"
 
-SOURCES = ["api.hip", "gemm.hip", "attn_fwd.hip", "attn_fwd_half.hip", "attn_bwd.hip", "attn_bwd_short.hip", "attn_bwd_kv.hip",
+SOURCES = ["api.hip", "gemm.hip", "gemm_pair.hip", "attn_fwd.hip", "attn_fwd_half.hip", "attn_bwd.hip", "attn_bwd_short.hip", "attn_bwd_kv.hip",
            "attn_bwd_half.hip", "attn_bwd_dq.hip", "attn_bwd_dq_half.hip", "prologue.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -409,29 +409,21 @@ laga_status_t laga_attn_bwd_stage(int stage, const laga_problem_t* p, const void
   a.delta = (float*)(wsb + ws.delta); a.dkv = wsb + ws.dkv; a.dkpe_h = (float*)(wsb + ws.dkpe_h);
   a.lse2 = (float*)(wsb + ws.lse2); a.S_pad = s_pad(d.S);
   a.dkv_lo = bf ? wsb + ws.dkv_lo : nullptr;
-  a.dk_pe = dk_pe;
   a.ds = stores_ds(p) ? wsb + ws.ds : nullptr;
   a.B = d.B; a.S = d.S; a.H = d.H; a.scale = p->softmax_scale; a.causal = p->causal;
+  if (stage == LAGA_BWD_FINISH) {
+    FinishParams f{};
+    f.dkv = a.dkv; f.dkv_lo = a.dkv_lo; f.w = w_kv_b; f.c_kv = c_kv; f.dkpe_h = a.dkpe_h;
+    f.dc = dc_kv; f.dw = dw_kv_b; f.dk_pe = dk_pe; f.partial = (float*)(wsb + ws.dw_part);
+    f.tokens = d.B * d.S; f.d_c = d.d_c; f.ncol = d.H * d.dkvh(); f.H = d.H; f.d_rope = d.dr;
+    return from_hip(bf ? launch_finish<bf16>(f, st) : launch_finish<float>(f, st));
+  }
   hipError_t e;
-  const int kstage = stage == LAGA_BWD_PREPARE ? 0 : stage == LAGA_BWD_DKDV ? 1 : stage == LAGA_BWD_DQ ? 2 : 3;
+  const int kstage = stage == LAGA_BWD_PREPARE ? 0 : stage == LAGA_BWD_DKDV ? 1 : 2;
   if (v3) e = bf ? launch_attn_bwd<bf16, 128, 64, 128>(a, kstage, st) : launch_attn_bwd<float, 128, 64, 128>(a, kstage, st);
   else if (is_half(p))
     e = bf ? launch_attn_bwd<bf16, 64, 32, 64>(a, kstage, st) : launch_attn_bwd<float, 64, 32, 64>(a, kstage, st);
   else e = bf ? launch_attn_bwd<bf16, 32, 16, 32>(a, kstage, st) : launch_attn_bwd<float, 32, 16, 32>(a, kstage, st);
-  if (e != hipSuccess || stage != LAGA_BWD_FINISH) return from_hip(e);
-
-  const int tok = d.B * d.S, ncol = d.H * d.dkvh();
-  float* part = (float*)(wsb + ws.dw_part);
-  if (bf) {
-    const bf16* hi = (const bf16*)a.dkv;
-    const bf16* lo = (const bf16*)a.dkv_lo;
-    e = launch_dc<bf16>(hi, lo, (const bf16*)w_kv_b, dc_kv, part, tok, d.d_c, ncol, st);
-    if (e == hipSuccess) e = launch_dw<bf16>((const bf16*)c_kv, hi, lo, dw_kv_b, part, d.d_c, ncol, tok, st);
-  } else {
-    const float* g = (const float*)a.dkv;
-    e = launch_dc<float>(g, nullptr, (const float*)w_kv_b, dc_kv, part, tok, d.d_c, ncol, st);
-    if (e == hipSuccess) e = launch_dw<float>((const float*)c_kv, g, nullptr, dw_kv_b, part, d.d_c, ncol, tok, st);
-  }
   return from_hip(e);
 }
 

@@ -17,7 +17,6 @@
 //                  accumulators, with dO^T / Q^T read by transposing LDS reads;
 //                  software-pipelined on the 32x32x16 MFMA (see there); unless dq is
 //                  to be recomputed, it also stores dS^T for the dQ pass
-//   dkpe_kernel    dk_pe = sum over heads (ascending) of the per-head k_pe parts
 // in attn_bwd_kv.hip: dkdv_kernel, the same key-stationary pass for the other element
 // types and head widths; and in attn_bwd_dq.hip: dq_kernel (query-stationary: a
 // workgroup owns 32*WPH queries of one head and sweeps the key tiles up to the
@@ -687,19 +686,6 @@ __global__ __launch_bounds__(256, 1) void dkdv32_kernel(BwdParams P) {
 }
 
 
-// dk_pe[b,t,:] = sum_{h ascending} dkpe_h[b,t,h,:]   (one thread per 4 outputs, fp32)
-template <int DR>
-__global__ __launch_bounds__(256) void dkpe_kernel(const float* __restrict__ part, float* __restrict__ dkpe, int H,
-                                                   int n4) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n4) return;
-  const int bt = i / (DR / 4), c = (i % (DR / 4)) * 4;
-  const float* src = part + (size_t)bt * H * DR + c;
-  f32x4 s = *reinterpret_cast<const f32x4*>(src);
-  for (int h = 1; h < H; ++h) s += *reinterpret_cast<const f32x4*>(src + (size_t)h * DR);
-  *reinterpret_cast<f32x4*>(dkpe + (size_t)bt * DR + c) = s;
-}
-
 }  // namespace
 
 #ifndef LAGA_SHORT_SEQ
@@ -750,11 +736,8 @@ hipError_t launch_attn_bwd(const AttnBwdArgs& a, int stage, hipStream_t st) {
     } else {
       return launch_dkdv_generic<T, DN, DR, DV>(P, a.B, st);
     }
-  } else if (stage == 2) {
-    return launch_bwd_dq<T, DN, DR, DV>(P, a.B, st);
   } else {
-    const int n4 = a.B * a.S * DR / 4;
-    dkpe_kernel<DR><<<(n4 + 255) / 256, 256, 0, st>>>(a.dkpe_h, a.dk_pe, a.H, n4);
+    return launch_bwd_dq<T, DN, DR, DV>(P, a.B, st);
   }
   return hipGetLastError();
 }

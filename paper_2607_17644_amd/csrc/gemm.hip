@@ -304,10 +304,24 @@ struct GRead {
 // copies in-bounds rows (k-strided) or chunks (k-contiguous) in the place of the missing
 // ones, k-strided rows past the end are zeroed in LDS before they are read, and a second
 // 16-wide step with nothing in it is left out.
+constexpr int ring_stage(int BM, int BN, int SPLIT) {  // LDS elements of a stage
+  return (BM + BN + (SPLIT == 1 ? BM : SPLIT == 2 ? BN : 0)) * kGK;
+}
+// A kernel here; in gemm_pair.hip the same body is a function that one kernel calls for dc and
+// for dW (as a function called here too, its users' register allocation changes: dW 99 -> 109
+// us at 2 x 5001 tokens).
 template <int BM, int BN, int NWV, int WGM, int NSLOT, bool A_KS, bool B_KS, int SPLIT, typename TO>
+#ifndef LAGA_GEMM_PAIR
 __global__ __launch_bounds__(64 * NWV, NWV == 4 ? 2 : 1) void gemm_ring_kernel(
     const bf16* __restrict__ A, const bf16* __restrict__ B, const bf16* __restrict__ X2, TO* __restrict__ C,
     int M, int N, int K, int lda, int ldb, int ldc, int k_chunk, long long split_stride) {
+  __shared__ __attribute__((aligned(16))) bf16 sm[NSLOT * ring_stage(BM, BN, SPLIT)];
+  const int tile = blockIdx.x, split = blockIdx.z;
+#else
+__device__ __forceinline__ void gemm_ring_tile(bf16* sm, const int tile, const int split, const bf16* A,
+                                               const bf16* B, const bf16* X2, TO* C, int M, int N, int K, int lda,
+                                               int ldb, int ldc, int k_chunk, long long split_stride) {
+#endif
   constexpr int WGN = NWV / WGM;                 // waves along n (WGM along m)
   constexpr int WTM = BM / WGM, WTN = BN / WGN;  // one wave's output tile
   constexpr int NI = WTM / 32, NJ = WTN / 32;    // its 32 x 32 blocks
@@ -317,13 +331,13 @@ __global__ __launch_bounds__(64 * NWV, NWV == 4 ? 2 : 1) void gemm_ring_kernel(
   constexpr int XB = SPLIT == 1 ? NI : NJ;       // X2 blocks per wave
   constexpr int TA = BM * kGK, TB = BN * kGK, TX = SPLIT ? XR * kGK : 0;
   constexpr int STAGE = TA + TB + TX;
-  __shared__ __attribute__((aligned(16))) bf16 sm[NSLOT * STAGE];
+  static_assert(STAGE == ring_stage(BM, BN, SPLIT), "stage size");
 
   const int n_tiles = (N + BN - 1) / BN, m_tiles = (M + BM - 1) / BM;
-  const int lin = xcd_remap_any(blockIdx.x, n_tiles * m_tiles);
+  const int lin = xcd_remap_any(tile, n_tiles * m_tiles);
   const int tn = lin % n_tiles, tm = lin / n_tiles;
   const int m0 = tm * BM, n0 = tn * BN;
-  const int kb = blockIdx.z * k_chunk;
+  const int kb = split * k_chunk;
   const int klen = min(K, kb + k_chunk) - kb;
   const int nst = (klen + kGK - 1) / kGK;
   const int tail = klen - (nst - 1) * kGK;  // contraction indices of the last stage, 1 .. 32
@@ -456,7 +470,7 @@ __global__ __launch_bounds__(64 * NWV, NWV == 4 ? 2 : 1) void gemm_ring_kernel(
   mmas(0);
   if (tail > 16) mmas(1);
 
-  TO* Cz = C + blockIdx.z * split_stride;
+  TO* Cz = C + split * split_stride;
 #pragma unroll
   for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -472,6 +486,8 @@ __global__ __launch_bounds__(64 * NWV, NWV == 4 ? 2 : 1) void gemm_ring_kernel(
       }
     }
 }
+
+#ifndef LAGA_GEMM_PAIR
 
 // ------------------------------------------------------------------ streamed large tiles (bf16 out)
 // The 256 x 256 tile (no split, bf16 output) for a short contraction such as the
@@ -710,6 +726,42 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const float* __restri
 template <typename T> struct GemmCfg;
 template <> struct GemmCfg<float> { static constexpr int BM = 64, BN = 64, BK = 16; };
 
+// The backward's last launch: dc and dW from their split partials (ascending splits) and
+// dk_pe[t, :] = sum over heads (ascending) of the per-head parts, 4 values per thread. One
+// launch for the three: each alone is mostly launch and drain (5 to 7 us at 1000 tokens).
+struct FinishArgs {
+  const float *dc_part, *dw_part, *dkpe_h;
+  float *dc, *dw, *dk_pe;
+  long long n_dc, n_dw;          // float4 of dc, of dW (0: nothing to sum)
+  int dc_splits, dw_splits, H, dr4;  // dr4: float4 per dk_pe row
+  long long n_pe;                // float4 of dk_pe
+  unsigned b_dc, b_dw;           // workgroups of dc, of dW; the rest dk_pe
+};
+__global__ __launch_bounds__(256) void finish_reduce_kernel(FinishArgs a) {
+  const unsigned blk = blockIdx.x;
+  auto sum = [](const float* src, float* dst, long long i, int n, long long stride4) {
+    const f32x4* p = reinterpret_cast<const f32x4*>(src) + i;
+    f32x4 s = p[0];
+    for (int k = 1; k < n; ++k) s += p[k * stride4];
+    reinterpret_cast<f32x4*>(dst)[i] = s;
+  };
+  if (blk < a.b_dc) {
+    const long long i = (long long)blk * 256 + threadIdx.x;
+    if (i < a.n_dc) sum(a.dc_part, a.dc, i, a.dc_splits, a.n_dc);
+  } else if (blk < a.b_dc + a.b_dw) {
+    const long long i = (long long)(blk - a.b_dc) * 256 + threadIdx.x;
+    if (i < a.n_dw) sum(a.dw_part, a.dw, i, a.dw_splits, a.n_dw);
+  } else {
+    const long long i = (long long)(blk - a.b_dc - a.b_dw) * 256 + threadIdx.x;
+    if (i >= a.n_pe) return;
+    const long long row = i / a.dr4;
+    const f32x4* p = reinterpret_cast<const f32x4*>(a.dkpe_h) + row * a.H * a.dr4 + i % a.dr4;
+    f32x4 s = p[0];
+    for (int h = 1; h < a.H; ++h) s += p[h * a.dr4];
+    reinterpret_cast<f32x4*>(a.dk_pe)[i] = s;
+  }
+}
+
 inline int grid_tiles(int M, int N, int BM, int BN) { return ((M + BM - 1) / BM) * ((N + BN - 1) / BN); }
 constexpr int kCUs = 256;  // compute units of the gfx950 part (one large-tile workgroup each)
 
@@ -796,83 +848,124 @@ namespace {
 size_t dw_partial_elems(int tokens, int d_c, int K) {
   return dw_split_count(tokens) > 1 ? dw_split_count(tokens) * (size_t)d_c * K : 0;
 }
+// dc and dW share a launch up to this many 128 x 128 workgroups (two per CU).
+constexpr int kPairMaxGroups = 2 * kCUs;
 bool dc_wide(int tokens, int d_c) { return grid_tiles(tokens, d_c, 128, 128) > kCUs + kCUs / 8; }
-}  // namespace
-
-int dc_split_count(int tokens, int d_c, int K) {
-  const bool wide = dc_wide(tokens, d_c);
-  const int tiles = !wide       ? grid_tiles(tokens, d_c, 128, 128)
+// Partials that dc may have beside dW's (floats; 128 x 128 tiles, where one last launch sums
+// both). The sum of both stays within max(dW's, the splits of a 512-workgroup grid or of 128 x
+// 512 tiles, at least 256 indices each), so that every problem whose workspace fits the fixed
+// array of laga_attn_bwd_noalloc keeps fitting it.
+size_t dc_partial_room(int tokens, int d_c, int K) {
+  const bool aligned = tokens % 8 == 0;
+  const int tiles = !aligned    ? grid_tiles(tokens, d_c, 128, 128)
                     : d_c > 256 ? grid_tiles(tokens, d_c, 128, 512)
                                 : grid_tiles(tokens, d_c, 256, 256);
-  const int max_split = K >= 1024 ? K / 512 : 1;
-  int n = kCUs / tiles;
-  if (wide) n = min(n, (int)(dw_partial_elems(tokens, d_c, K) / ((size_t)tokens * d_c)));
-  return n < 1 ? 1 : (n > max_split ? max_split : n);
+  const int want = aligned ? kCUs : 2 * kCUs, most = K >= 512 ? K / 256 : 1;
+  const int n = min((want + tiles - 1) / tiles, most);
+  const size_t cap = n > 1 ? (size_t)n * tokens * d_c : 0, dw = dw_partial_elems(tokens, d_c, K);
+  return cap > dw ? cap - dw : 0;
 }
+}  // namespace
+
+namespace {
+// Splits of dc's contraction, and whether dc and dW share a launch (gemm_pair.hip): when the
+// 128 x 128 tiles of both fit the chip at once and the workspace has room for the partials of
+// both (a quarter fewer splits of dc than wanted is a fair price); the last launch then sums
+// both. Otherwise dc's partials lie in the place of dW's and are summed right away, while they
+// are in cache (2048 tokens, 16 heads: left to the last launch 5 us slower). Measured, the
+// whole stage (us, apart / shared): 16 heads 100 tokens 26 / 17, 300 31 / 20, 1000 47 / 37, 8
+// heads 1000 36 / 23; half-width heads, 4 x 2000 68 / 59.
+struct DcPlan {
+  bool wide, pair;
+  int splits;
+};
+DcPlan dc_plan(int tokens, int d_c, int K) {
+  DcPlan p{};
+  p.wide = dc_wide(tokens, d_c);
+  const int tiles = !p.wide     ? grid_tiles(tokens, d_c, 128, 128)
+                    : d_c > 256 ? grid_tiles(tokens, d_c, 128, 512)
+                                : grid_tiles(tokens, d_c, 256, 256);
+  const size_t each = (size_t)tokens * d_c;
+  int n = min(kCUs / tiles, K >= 1024 ? K / 512 : 1);
+  if (p.wide) n = min(n, (int)(dw_partial_elems(tokens, d_c, K) / each));
+  p.splits = n < 1 ? 1 : n;
+  if (!p.wide) {
+    const int fit = min(p.splits, (int)(dc_partial_room(tokens, d_c, K) / each));
+    const int ns = p.splits == 1 || 4 * fit < 3 * p.splits ? p.splits : fit;
+    p.pair = (p.splits == 1 || 4 * fit >= 3 * p.splits) &&
+             tiles * ns + grid_tiles(d_c, K, 128, 128) * (int)dw_split_count(tokens) <= kPairMaxGroups;
+    if (p.pair) p.splits = ns;
+  }
+  return p;
+}
+}  // namespace
+
 size_t gemm_partial_elems(int tokens, int d_c, int K) {
-  const size_t dw = dw_partial_elems(tokens, d_c, K);
-  const int ndc = dc_split_count(tokens, d_c, K);
-  const size_t dc = ndc > 1 ? (size_t)ndc * tokens * d_c : 0;
-  return dw > dc ? dw : dc;
+  const DcPlan p = dc_plan(tokens, d_c, K);
+  const size_t dw = dw_partial_elems(tokens, d_c, K), dc = p.splits > 1 ? (size_t)p.splits * tokens * d_c : 0;
+  return p.pair ? dw + dc : dw > dc ? dw : dc;
 }
 
 template <typename T>
-hipError_t launch_dc(const T* dkv, const T* dkv_lo, const T* w, float* dc, float* partial, int M, int N, int K,
-                     hipStream_t st) {
-  // dc[M=tokens][N=d_c] = (dKV + dKV_lo)[M][K=H*dkvh] @ W^T ; W stored [N][K] (k-contiguous).
-  // With a split contraction each split writes its partial and a fixed-order reduce sums them.
+hipError_t launch_finish(const FinishParams& f, hipStream_t st) {
+  // dc[tokens][d_c] = (dKV + dKV_lo)[tokens][ncol] @ W^T, W stored [d_c][ncol] (k-contiguous);
+  // dW[d_c][ncol] = c^T @ (dKV + dKV_lo), c stored [tokens][d_c] and dKV [tokens][ncol] (both
+  // k-strided). Split contractions write partials that the last launch sums in a fixed order.
+  const T *dkv = (const T*)f.dkv, *w = (const T*)f.w, *c = (const T*)f.c_kv;
+  const int M = f.tokens, N = f.d_c, K = f.ncol;
+  const int split = dw_split_tokens(M), nw = (int)dw_split_count(M);
+  float* dw_part = f.partial;
+  const DcPlan plan = dc_plan(M, N, K);
+  float* dc_part = f.partial + (plan.pair ? dw_partial_elems(M, N, K) : 0);
+  const long long sdc = (long long)M * N, sdw = (long long)N * K;
+  int nz = 1;  // splits of dc
   if constexpr (sizeof(T) == 2) {
-    const int nsplit = dc_split_count(M, N, K);
-    const int k_chunk = (K / nsplit + kGK - 1) / kGK * kGK;
-    const int nz = (K + k_chunk - 1) / k_chunk;
-    float* target = nz == 1 ? dc : partial;
-    const long long stride = (long long)M * N;
-    if (!dc_wide(M, N))
-      gemm_ring_kernel<128, 128, 4, 2, 3, false, false, 1, float><<<dim3(grid_tiles(M, N, 128, 128), 1, nz), 256, 0,
-                                                                     st>>>(dkv, w, dkv_lo, target, M, N, K, K, K, N,
-                                                                           k_chunk, stride);
-    else if (N > 256)
-      gemm_ring_kernel<128, 512, 8, 2, 3, false, false, 1, float><<<dim3(grid_tiles(M, N, 128, 512), 1, nz), 512, 0,
-                                                                     st>>>(dkv, w, dkv_lo, target, M, N, K, K, K, N,
-                                                                           k_chunk, stride);
-    else
-      gemm_ring_kernel<256, 256, 8, 2, 3, false, false, 1, float><<<dim3(grid_tiles(M, N, 256, 256), 1, nz), 512, 0,
-                                                                     st>>>(dkv, w, dkv_lo, target, M, N, K, K, K, N,
-                                                                           k_chunk, stride);
-    if (nz > 1) {
-      const long long n4 = stride / 4;
-      split_reduce_kernel<<<(unsigned)((n4 + 255) / 256), 256, 0, st>>>(partial, dc, n4, nz, stride);
+    const T* lo = (const T*)f.dkv_lo;
+    const int k_chunk = (K / plan.splits + kGK - 1) / kGK * kGK;
+    nz = (K + k_chunk - 1) / k_chunk;
+    float *dc = nz == 1 ? f.dc : dc_part, *dw = nw == 1 ? f.dw : dw_part;
+    const int tdc = grid_tiles(M, N, 128, 128), tdw = grid_tiles(N, K, 128, 128);
+    if (plan.pair) {
+      const GemmPairArgs a = {dkv, lo, w, c, dc, dw, M, N, K, k_chunk, split, tdc, tdw, tdc * nz};
+      launch_gemm_pair(a, tdc * nz + tdw * nw, st);
+    } else {
+      if (!plan.wide)
+        gemm_ring_kernel<128, 128, 4, 2, 3, false, false, 1, float><<<dim3(tdc, 1, nz), 256, 0, st>>>(
+            dkv, w, lo, dc, M, N, K, K, K, N, k_chunk, sdc);
+      else if (N > 256)
+        gemm_ring_kernel<128, 512, 8, 2, 3, false, false, 1, float><<<dim3(grid_tiles(M, N, 128, 512), 1, nz), 512, 0,
+                                                                       st>>>(dkv, w, lo, dc, M, N, K, K, K, N, k_chunk,
+                                                                             sdc);
+      else
+        gemm_ring_kernel<256, 256, 8, 2, 3, false, false, 1, float><<<dim3(grid_tiles(M, N, 256, 256), 1, nz), 512, 0,
+                                                                       st>>>(dkv, w, lo, dc, M, N, K, K, K, N, k_chunk,
+                                                                             sdc);
+      if (nz > 1) {  // dW's partials take their place
+        split_reduce_kernel<<<(unsigned)((sdc / 4 + 255) / 256), 256, 0, st>>>(dc_part, f.dc, sdc / 4, nz, sdc);
+        nz = 1;
+      }
+      if (N > 256)
+        launch_ring<512, 128, true, true, 2, float>(c, dkv, lo, dw, N, K, M, N, K, K, split, nw, st);
+      else
+        launch_ring<256, 256, true, true, 2, float>(c, dkv, lo, dw, N, K, M, N, K, K, split, nw, st);
     }
   } else {
     using G = GemmCfg<T>;
     gemm_kernel<T, float, false, false, G::BM, G::BN, G::BK><<<grid_tiles(M, N, G::BM, G::BN), kThreads, 0, st>>>(
-        dkv, w, dc, M, N, K, K, K, N, K, 0);
+        dkv, w, f.dc, M, N, K, K, K, N, K, 0);
+    gemm_kernel<T, float, true, true, G::BM, G::BN, G::BK><<<dim3(grid_tiles(N, K, G::BM, G::BN), 1, nw), kThreads, 0,
+                                                             st>>>(c, dkv, nw == 1 ? f.dw : dw_part, N, K, M, N, K, K,
+                                                                   split, sdw);
   }
-  return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_dw(const T* c, const T* dkv, const T* dkv_lo, float* dw, float* partial, int M, int N, int K,
-                     hipStream_t st) {
-  // dW[M=d_c][N=H*dkvh] = c^T @ (dKV + dKV_lo); c stored [K=tokens][M] and dKV [K][N]: both k-strided.
-  const int split = dw_split_tokens(K);
-  const int nsplit = (int)dw_split_count(K);
-  float* target = nsplit == 1 ? dw : partial;
-  if constexpr (sizeof(T) == 2) {
-    if (M > 256)
-      launch_ring<512, 128, true, true, 2, float>(c, dkv, dkv_lo, target, M, N, K, M, N, N, split, nsplit, st);
-    else
-      launch_ring<256, 256, true, true, 2, float>(c, dkv, dkv_lo, target, M, N, K, M, N, N, split, nsplit, st);
-  } else {
-    using G = GemmCfg<T>;
-    gemm_kernel<T, float, true, true, G::BM, G::BN, G::BK><<<dim3(grid_tiles(M, N, G::BM, G::BN), 1, nsplit), kThreads,
-                                                             0, st>>>(c, dkv, target, M, N, K, M, N, N, split,
-                                                                      (long long)M * N);
-  }
-  if (nsplit > 1) {
-    const long long n4 = (long long)M * N / 4;
-    split_reduce_kernel<<<(unsigned)((n4 + 255) / 256), 256, 0, st>>>(partial, dw, n4, nsplit, (long long)M * N);
-  }
+  FinishArgs a{};
+  a.dc_part = dc_part; a.dw_part = dw_part; a.dkpe_h = f.dkpe_h; a.dc = f.dc; a.dw = f.dw; a.dk_pe = f.dk_pe;
+  a.n_dc = nz > 1 ? sdc / 4 : 0;
+  a.n_dw = nw > 1 ? sdw / 4 : 0;
+  a.dc_splits = nz; a.dw_splits = nw; a.H = f.H; a.dr4 = f.d_rope / 4;
+  a.n_pe = (long long)M * a.dr4;
+  a.b_dc = (unsigned)((a.n_dc + 255) / 256);
+  a.b_dw = (unsigned)((a.n_dw + 255) / 256);
+  finish_reduce_kernel<<<a.b_dc + a.b_dw + (unsigned)((a.n_pe + 255) / 256), 256, 0, st>>>(a);
   return hipGetLastError();
 }
 
@@ -928,11 +1021,10 @@ template hipError_t launch_gemm_tn<float>(const float*, const float*, float*, fl
                                           hipStream_t);
 template hipError_t launch_reconstruct<bf16>(const bf16*, const bf16*, bf16*, int, int, int, hipStream_t);
 template hipError_t launch_reconstruct<float>(const float*, const float*, float*, int, int, int, hipStream_t);
-template hipError_t launch_dc<bf16>(const bf16*, const bf16*, const bf16*, float*, float*, int, int, int, hipStream_t);
-template hipError_t launch_dc<float>(const float*, const float*, const float*, float*, float*, int, int, int,
-                                     hipStream_t);
-template hipError_t launch_dw<bf16>(const bf16*, const bf16*, const bf16*, float*, float*, int, int, int, hipStream_t);
-template hipError_t launch_dw<float>(const float*, const float*, const float*, float*, float*, int, int, int,
-                                     hipStream_t);
+template hipError_t launch_finish<bf16>(const FinishParams&, hipStream_t);
+template hipError_t launch_finish<float>(const FinishParams&, hipStream_t);
 
+#else
+}  // namespace
+#endif  // LAGA_GEMM_PAIR
 }  // namespace laga

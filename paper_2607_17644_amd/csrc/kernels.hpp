@@ -15,22 +15,36 @@ constexpr int kRowPad = 64;
 // computes it. 2048 for long sequences, down to 512 for short ones (enough workgroups).
 int dw_split_tokens(int tokens);
 size_t dw_split_count(int tokens);
-// Splits of the dc_kv GEMM's contraction (over the shard's heads x 256), chosen so that
-// the launch has enough workgroups; dc_kv sums over heads, so no bit-identity across
-// head shards is asked of it. Partials of both GEMMs share one workspace buffer.
-int dc_split_count(int tokens, int d_c, int K);
+// Workspace of the split partials of dc_kv (its contraction, over the shard's heads x 256, is
+// split so that the launch has enough workgroups; dc_kv sums over heads, so no bit-identity
+// across head shards is asked of it) and of dW.
 size_t gemm_partial_elems(int tokens, int d_c, int K);
 
 template <typename T>
 hipError_t launch_reconstruct(const T* c, const T* w, T* kv, int M, int N, int K, hipStream_t st);
-// dkv_lo (may be NULL): low bf16 halves of dKV, so that dKV = dkv + dkv_lo to ~16 bits.
-// partial: workspace of gemm_partial_elems floats (used when the contraction is split).
+// Last stage of the backward: dc_kv, dW and the head sum dk_pe.
+struct FinishParams {
+  const void* dkv;      // [tokens][ncol = H*(d_nope+d_v)]
+  const void* dkv_lo;   // bf16: low halves, so that dKV = dkv + dkv_lo to ~16 bits (fp32: unused)
+  const void* w;        // W_kv_b [d_c][ncol]
+  const void* c_kv;     // [tokens][d_c]
+  const float* dkpe_h;  // [tokens][H][d_rope]
+  float* dc;            // [tokens][d_c]
+  float* dw;            // [d_c][ncol]
+  float* dk_pe;         // [tokens][d_rope]
+  float* partial;       // workspace of gemm_partial_elems floats
+  int tokens, d_c, ncol, H, d_rope;
+};
 template <typename T>
-hipError_t launch_dc(const T* dkv, const T* dkv_lo, const T* w, float* dc, float* partial, int M, int N, int K,
-                     hipStream_t st);
-template <typename T>
-hipError_t launch_dw(const T* c, const T* dkv, const T* dkv_lo, float* dw, float* partial, int M, int N, int K,
-                     hipStream_t st);
+hipError_t launch_finish(const FinishParams& f, hipStream_t st);
+// its dc and dW GEMMs in one launch (gemm_pair.hip): workgroups [0, n_dc) are dc's tiles
+// (tiles_dc per split), the others dW's
+struct GemmPairArgs {
+  const bf16 *dkv, *dkv_lo, *w, *c;
+  float *dc, *dw;  // targets (partials when their contraction is split)
+  int tokens, d_c, ncol, chunk_dc, chunk_dw, tiles_dc, tiles_dw, n_dc;
+};
+void launch_gemm_pair(const GemmPairArgs& a, int groups, hipStream_t st);
 
 // Plain GEMMs of the output projection (Alg. 1 step 7) on the same kernels:
 //   gemm_nt: c[M][N] = a[M][K] @ w^T, w stored [N][K]; element-dtype output
@@ -88,7 +102,6 @@ struct AttnBwdArgs {
   const void* dout;
   const float* lse;
   void* dq;          // [B,S,H,DN+DR]
-  float* dk_pe;      // [B,S,DR] fp32
   float* delta;      // workspace [B*H][S_pad]
   float* lse2;       // workspace [B*H][S_pad]: lse * log2(e)
   int S_pad;         // S rounded up to kRowPad
@@ -117,8 +130,7 @@ hipError_t launch_dkdv_generic(bwd::BwdParams P, int B, hipStream_t st);
 // the same for bf16 with 64/32/64-wide heads (attn_bwd_half.hip)
 hipError_t launch_dkdv_half(bwd::BwdParams P, int B, hipStream_t st);
 
-// stage 0: delta; 1: dK/dV (into dkv, dkpe_h); 2: dQ; 3: dk_pe head sum.
-// (dc_kv / dW are the GEMMs above.)
+// stage 0: delta; 1: dK/dV (into dkv, dkpe_h); 2: dQ. (The last stage is launch_finish.)
 template <typename T, int DN, int DR, int DV>
 hipError_t launch_attn_bwd(const AttnBwdArgs& a, int stage, hipStream_t st);
 
