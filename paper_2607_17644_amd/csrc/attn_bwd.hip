@@ -18,9 +18,10 @@
 //                  software-pipelined on the 32x32x16 MFMA (see there); unless dq is
 //                  to be recomputed, it also stores dS^T for the dQ pass
 // in attn_bwd_kv.hip: dkdv_kernel, the same key-stationary pass for the other element
-// types and head widths; and in attn_bwd_dq.hip: dq_kernel (query-stationary: a
-// workgroup owns 32*WPH queries of one head and sweeps the key tiles up to the
-// diagonal, recomputing S and dP - the price of not accumulating dQ with atomics), and
+// types and head widths (attn_bwd_half.hip: bf16 at 64/32/64); and in attn_bwd_dq.hip:
+// dq_kernel (query-stationary: a workgroup owns 64 queries of one head and sweeps the key
+// tiles up to the diagonal, recomputing S and dP - the price of not accumulating dQ with
+// atomics), and
 // for bf16 with 192/128-wide heads dq_ds_kernel (dQ as a product over the stored dS^T),
 // dq_rec_kernel (dQ recomputed, no S x S buffer) and the fused-mode dQ kernels that
 // rebuild K from the latent.
@@ -716,7 +717,6 @@ hipError_t launch_dkdv32_short(BwdParams P, int B, hipStream_t st) {
 #ifndef LAGA_SHORT_SEQ
 template <typename T, int DN, int DR, int DV>
 hipError_t launch_attn_bwd(const AttnBwdArgs& a, int stage, hipStream_t st) {
-  using Tl = BwdTiles<T>;
   BwdParams P;
   P.q = a.q; P.k_pe = a.k_pe; P.kv = a.kv; P.dout = a.dout; P.lse = a.lse; P.delta = a.delta;
   P.lse2 = a.lse2; P.S_pad = a.S_pad;

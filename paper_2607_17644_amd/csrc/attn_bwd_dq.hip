@@ -17,16 +17,27 @@ using namespace bwd;
 namespace {
 
 // ------------------------------------------------------------------ dQ
-template <typename T, int DN, int DR, int DV, int BC, int WPH>
-__global__ __launch_bounds__(64 * WPH) void dq_kernel(BwdParams P) {
-  constexpr int DQK = DN + DR, DKVH = DN + DV, DQK32 = round32(DQK);
-  constexpr int NT = 64 * WPH, BR = 32 * WPH, E = Elems16<T>::n;
+// A workgroup of four waves owns 64 queries of one head: waves 0, 1 take the even 32-key tiles,
+// waves 2, 3 the odd ones for the same queries (32 per wave; Q, dO and the dQ^T accumulators in
+// registers), and the two partial sums meet in LDS at the end. As in the generic dK/dV kernel
+// the work on a tile is split in two, A: S^T = K Q^T, P and half of dP^T = V dO^T, C: the rest of
+// dP^T and dQ^T += K^T dS^T, phase p runs A of tile p on one pair beside C of tile p - 1 on the other, and
+// tiles stream through three LDS slots of direct global->LDS copies. The chain of key tiles of
+// the last queries is the kernel's time when there are no more workgroups than CUs; the pairs
+// halve it. Before (128 queries per workgroup, each wave on every tile, tiles staged through
+// registers) / now, us, fp32: 2048 tokens, 16 heads of 192/128 561 / 320, 32 heads x 4000 2326
+// / 2282; 256 tokens, 4 heads of 48/32 27 / 20; 4 x 2000 tokens, 16 heads of 96/64 607 / 639 (the
+// same step's dK/dV gains 105).
+template <typename T, int DN, int DR, int DV>
+__global__ __launch_bounds__(256, DN == 128 ? 1 : 2) void dq_kernel(BwdParams P) {
+  constexpr int DQK = DN + DR, DKVH = DN + DV, DQK32 = round32(DQK), NDQ = DQK32 / 32;
+  constexpr int BR = 64, BC = 32, NS = 3, E = Elems16<T>::n;
   constexpr int PK = lds_pitch<T>(DQK32), PV = lds_pitch<T>(DV);
-  constexpr int KCH = DQK / E, VCH = DV / E;
-  constexpr int TILE_CHUNKS = BC * (KCH + VCH);
-  constexpr int PER_THREAD = (TILE_CHUNKS + NT - 1) / NT;
-  __shared__ __attribute__((aligned(16))) T sK[BC * PK];
-  __shared__ __attribute__((aligned(16))) T sV[BC * PV];
+  constexpr int KCH = DQK / E, VCH = DV / E, NCH = DN / E;  // chunks per row
+  static_assert(KCH <= 64 && VCH <= 64, "one copy instruction per row");
+  constexpr int TK = BC * PK, TV = BC * PV;
+  __shared__ __attribute__((aligned(16))) T sm[NS * (TK + TV)];  // K slots, then V slots
+  T* const sVm = sm + NS * TK;
 
   const T* __restrict__ q = (const T*)P.q;
   const T* __restrict__ kpe = (const T*)P.k_pe;
@@ -39,15 +50,18 @@ __global__ __launch_bounds__(64 * WPH) void dq_kernel(BwdParams P) {
   qblk = P.n_blocks - 1 - qblk;
   const int b = bh / H, h = bh % H;
 
-  const int tid = threadIdx.x, wave = tid >> 6, l = tid & 63, n = l & 31, g = l >> 5;
-  const int q0 = qblk * BR + wave * 32;
+  const int tid = threadIdx.x, l = tid & 63, n = l & 31, g = l >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;
+  const int qs = wave & 1, tw = wave >> 1;
+  const int q0 = qblk * BR + qs * 32;
   const int my_q = q0 + n;
-  const int wg_qend = min(S, (qblk + 1) * BR);
-  const int kend = P.causal ? wg_qend : S;
+  const int kend = P.causal ? min(S, (qblk + 1) * BR) : S;
+  const int nt = (kend + BC - 1) / BC;
 
+  // zero the padding columns [DQK, DQK32) of every slot once: transposing reads touch them
   if (DQK32 > DQK)
-    for (int i = tid; i < BC * (DQK32 - DQK); i += NT)
-      sK[(i / (DQK32 - DQK)) * PK + DQK + i % (DQK32 - DQK)] = to_elem<T>(0.f);
+    for (int i = tid; i < NS * BC * (DQK32 - DQK); i += 256)
+      sm[(i / (DQK32 - DQK)) * PK + DQK + i % (DQK32 - DQK)] = to_elem<T>(0.f);
 
   frag_t<T> qf[DQK / 16], of[DV / 16];
   float lse2 = 0.f, dlt = 0.f;
@@ -74,100 +88,116 @@ __global__ __launch_bounds__(64 * WPH) void dq_kernel(BwdParams P) {
     }
   }
 
-  f32x16 dqa[DQK32 / 32];
+  f32x16 dqa[NDQ];
 #pragma unroll
-  for (int i = 0; i < DQK32 / 32; ++i)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) dqa[i][r] = 0.f;
+  for (int i = 0; i < NDQ; ++i) dqa[i] = f32x16{};
 
-  chunk16 stage[PER_THREAD];
-  auto load_tile = [&](int kt) {
+  // Slot <- key tile j: wave w copies rows 8 w .. of K = [K_nope || k_pe] and of V, one
+  // instruction per row (lane l chunk l); rows past S copy row S - 1 (masked below)
+  const T* kvh = kv + ((size_t)(b * S) * H + h) * DKVH;
+  const T* klane = l < NCH ? kvh + l * E : kpe + (size_t)(b * S) * DR + (l - NCH) * E;
+  const uint32_t kstep = l < NCH ? (uint32_t)(H * DKVH) : (uint32_t)DR;
+  auto fill = [&](int st, int j) {
+    const int kt = j * BC;
+    if (l < KCH)
 #pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const int c = tid + i * NT;
-      stage[i] = zero_chunk();
-      if (c < TILE_CHUNKS) {
-        const int row = c / (KCH + VCH), j = c % (KCH + VCH);
-        const int key = kt + row;
-        if (key < S) {
-          const size_t r = (size_t)(b * S + key);
-          const T* src = j < DN / E ? kv + (r * H + h) * DKVH + j * E
-                       : j < KCH    ? kpe + r * DR + (j - DN / E) * E
-                                    : kv + (r * H + h) * DKVH + DN + (j - KCH) * E;
-          stage[i] = *reinterpret_cast<const chunk16*>(src);
-        }
+      for (int i = 0; i < BC / 4; ++i) {
+        const int r = wave * (BC / 4) + i;
+        g2lds16(klane + (size_t)min(kt + r, S - 1) * kstep, sm + st * TK + r * PK);
       }
-    }
-  };
-  auto store_tile = [&]() {
+    if (l < VCH)
 #pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const int c = tid + i * NT;
-      if (c < TILE_CHUNKS) {
-        const int row = c / (KCH + VCH), j = c % (KCH + VCH);
-        T* dst = j < KCH ? sK + row * PK + j * E : sV + row * PV + (j - KCH) * E;
-        *reinterpret_cast<chunk16*>(dst) = stage[i];
+      for (int i = 0; i < BC / 4; ++i) {
+        const int r = wave * (BC / 4) + i;
+        g2lds16_so(kvh + (size_t)min(kt + r, S - 1) * H * DKVH + DN, 16u * l, sVm + st * TV + r * PV);
       }
-    }
   };
-
-  load_tile(0);
-  for (int kt = 0; kt < kend; kt += BC) {
-    __syncthreads();
-    store_tile();
-    __syncthreads();
-    if (kt + BC < kend) load_tile(kt + BC);
-
-    const bool active = q0 < S && (!P.causal || kt <= q0 + 31);
-    if (!active) continue;
+  // P and the first part of dP of the tile between its two halves: rows = keys (r/4)*8 + g*4 +
+  // r%4, column = my query. dP's products are dealt so that both halves have as many.
+  f32x16 sa, dp;
+  constexpr int NV1 = (DV / 16 + 2 * NDQ - DQK / 16) / 2;
+  static_assert(NV1 >= 0 && NV1 <= DV / 16, "dP steps of the first half");
+  auto half_a = [&](int st, int j) {
+    const T *sK = sm + st * TK, *sV = sVm + st * TV;
+    const int kt = j * BC;
+    sa = f32x16{};
+    dp = f32x16{};
+#pragma unroll
+    for (int ks = 0; ks < DQK / 16; ++ks) mma(sa, lds_frag<T>(sK + n * PK + ks * 16 + 8 * g), qf[ks]);
+#pragma unroll
+    for (int ks = 0; ks < NV1; ++ks) mma(dp, lds_frag<T>(sV + n * PV + ks * 16 + 8 * g), of[ks]);
     const bool need_mask = (P.causal && kt + BC - 1 > q0) || (kt + BC > S);
-
-    f32x16 sa[BC / 32], dp[BC / 32];
 #pragma unroll
-    for (int kb = 0; kb < BC / 32; ++kb) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) { sa[kb][r] = 0.f; dp[kb][r] = 0.f; }
-#pragma unroll
-      for (int ks = 0; ks < DQK / 16; ++ks)
-        mma(sa[kb], lds_frag<T>(sK + (kb * 32 + n) * PK + ks * 16 + 8 * g), qf[ks]);
-#pragma unroll
-      for (int ks = 0; ks < DV / 16; ++ks)
-        mma(dp[kb], lds_frag<T>(sV + (kb * 32 + n) * PV + ks * 16 + 8 * g), of[ks]);
-    }
-#pragma unroll
-    for (int kb = 0; kb < BC / 32; ++kb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        float p = fast_exp2(sa[kb][r] * P.scale_log2 - lse2);
-        if (need_mask) {
-          const int key = kt + kb * 32 + (r >> 2) * 8 + g * 4 + (r & 3);
-          if (key >= S || (P.causal && key > my_q)) p = 0.f;
-        }
-        dp[kb][r] = p * (dp[kb][r] - dlt);
+    for (int r = 0; r < 16; ++r) {
+      float p = fast_exp2(sa[r] * P.scale_log2 - lse2);
+      if (need_mask) {
+        const int key = kt + (r >> 2) * 8 + g * 4 + (r & 3);
+        if (key >= S || (P.causal && key > my_q)) p = 0.f;
       }
+      sa[r] = p;
+    }
+  };
+  auto half_c = [&](int st) {
+    const T *sK = sm + st * TK, *sV = sVm + st * TV;
+#pragma unroll
+    for (int ks = NV1; ks < DV / 16; ++ks) mma(dp, lds_frag<T>(sV + n * PV + ks * 16 + 8 * g), of[ks]);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dp[r] = sa[r] * (dp[r] - dlt);
 #pragma unroll
     for (int kk = 0; kk < BC / 16; ++kk) {
-      const frag_t<T> zf = acc_to_frag<T>(dp[kk >> 1], kk & 1);
+      const frag_t<T> zf = acc_to_frag<T>(dp, kk);
       const int ra = kk * 16 + 4 * g;
 #pragma unroll
-      for (int db = 0; db < DQK32 / 32; ++db) mma(dqa[db], TrRead<T>::get(sK, PK, ra, ra + 8, db * 32), zf);
+      for (int db = 0; db < NDQ; ++db) mma(dqa[db], TrRead<T>::get(sK, PK, ra, ra + 8, db * 32), zf);
     }
+  };
+  // start of phase p: tile p is there, tile p + 1 on its way into the slot of tile p - 2
+  auto phase = [&](int p) {
+    wait_vmem();      // this wave's copies of tile p have landed
+    __syncthreads();  // everyone's; tile p - 2 is no longer read
+    if (p + 1 < nt) fill((p + 1) % NS, p + 1);
+  };
+  fill(0, 0);
+  if (tw) phase(0);
+  for (int p = tw; p < nt; p += 2) {
+    const bool on = q0 < S && (!P.causal || p * BC <= q0 + 31);  // wave-uniform
+    phase(p);
+    if (on) half_a(p % NS, p);
+    phase(p + 1);
+    if (on) half_c(p % NS);
   }
+  if ((nt & 1) == tw) phase(nt);  // every wave goes through phases 0 .. nt
 
+  // even tiles + odd tiles: the first wave of a pair takes blocks [0, NDQ / 2) of the other's
+  // sum and stores them, the second the rest of the first's
+  __syncthreads();
+  constexpr int N0 = (NDQ + 1) / 2;
+  static_assert(2 * NDQ * 4096 <= (int)sizeof(T) * NS * (TK + TV), "partials fit the slots");
+  auto block = [&](int i) { return (float*)sm + (qs * NDQ + i) * 1024 + l * 4; };
+#pragma unroll
+  for (int i = 0; i < NDQ; ++i)
+    if ((i < N0) == (tw == 1))
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        *reinterpret_cast<f32x4*>(block(i) + r * 256) = f32x4{dqa[i][4 * r], dqa[i][4 * r + 1], dqa[i][4 * r + 2], dqa[i][4 * r + 3]};
+  __syncthreads();
   if (my_q >= S) return;
   T* dqr = (T*)P.dq + ((size_t)(b * S + my_q) * H + h) * DQK;
 #pragma unroll
-  for (int db = 0; db < DQK32 / 32; ++db)
+  for (int db = 0; db < NDQ; ++db) {
+    if ((db < N0) != (tw == 0)) continue;
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr) {
       const int d = db * 32 + rr * 8 + g * 4;
+      const f32x4 x = *reinterpret_cast<const f32x4*>(block(db) + rr * 256);
       if (d < DQK) {
         typename FragOf<T>::half v;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = to_elem<T>(dqa[db][4 * rr + e] * P.scale);
+        for (int e = 0; e < 4; ++e) v[e] = to_elem<T>((dqa[db][4 * rr + e] + x[e]) * P.scale);
         *reinterpret_cast<typename FragOf<T>::half*>(dqr + d) = v;
       }
     }
+  }
 }
 
 
@@ -831,9 +861,6 @@ constexpr long long kDqNarrowMaxGroups = 320;
 
 template <typename T, int DN, int DR, int DV>
 hipError_t launch_bwd_dq(bwd::BwdParams P, int B, hipStream_t st) {
-  using Tl = BwdTiles<T>;
-  constexpr int BR = 32 * Tl::WPH_Q;
-  P.n_blocks = (P.S + BR - 1) / BR;
   if constexpr (sizeof(T) == 2 && DN + DR == 192 && DV == 128) {
     if (P.ds) {
       if (P.w_t && P.d_c == kFusedMaxDc) {
@@ -864,7 +891,8 @@ hipError_t launch_bwd_dq(bwd::BwdParams P, int B, hipStream_t st) {
     dq_rec_kernel<DN, DR, DV, RW><<<dim3(P.n_blocks * P.H, B), 64 * RW, 0, st>>>(P);
     return hipGetLastError();
   }
-  dq_kernel<T, DN, DR, DV, Tl::BC, Tl::WPH_Q><<<dim3(P.n_blocks * P.H, B), 64 * Tl::WPH_Q, 0, st>>>(P);
+  P.n_blocks = (P.S + 63) / 64;
+  dq_kernel<T, DN, DR, DV><<<dim3(P.n_blocks * P.H, B), 256, 0, st>>>(P);
   return hipGetLastError();
 }
 

@@ -1,9 +1,7 @@
-// Generic key-stationary dK / dV kernel of the attention backward (the element types
-// and head widths without a tuned kernel: fp32, and bf16 at head widths other than
-// 192/128). Its own source file because it is compiled with the MFMA results in VGPRs
-// (no AGPR<->VGPR copies around the softmax arithmetic on the accumulators, and the
-// fp32 instance at 192/128-wide heads fits its 320 resident registers without spills),
-// a choice that makes the tuned bf16 kernel of attn_bwd.hip spill.
+// Generic key-stationary dK / dV kernel of the attention backward (fp32 at every head width,
+// and bf16 at 32/16/32-wide heads). Its own source file because it is compiled with the MFMA
+// results in VGPRs (no AGPR<->VGPR copies around the softmax arithmetic on the
+// accumulators), a choice that makes the tuned bf16 kernel of attn_bwd.hip spill.
 //
 // P = softmax(scale * Q K^T) is recomputed from the saved row log-sum-exp; per key
 // block: dV = P^T dO, dP = dO V^T, dZ = P * (dP - delta), dK = scale dZ^T Q (the
@@ -24,18 +22,30 @@ using namespace bwd;
 namespace {
 
 // ------------------------------------------------------------------ dK, dV
-template <typename T, int DN, int DR, int DV, int BQ, int WPH>
-__global__ __launch_bounds__(64 * WPH) void dkdv_kernel(BwdParams P) {
-  constexpr int DQK = DN + DR, DKVH = DN + DV, DQK32 = round32(DQK);
-  constexpr int BK = 32 * WPH, E = Elems16<T>::n;
+// A workgroup of four waves owns 64 keys of one head: waves 0, 1 take the even 32-query tiles,
+// waves 2, 3 the odd ones of the same keys (32 per wave; K, V and the dK^T / dV^T
+// accumulators in registers), and the two partial sums meet in LDS at the end. The work on a
+// tile has two equal halves - A: S = Q K^T, dP = dO V^T and the softmax, C: dV^T += dO^T P,
+// dK^T += Q^T dZ - and phase p runs A of tile p on one pair of waves beside C of tile p - 1 on
+// the other, so a tile is needed for two phases and three LDS slots do (fp32 tiles of 192/128
+// wide heads are 43 KB: a slot more would not fit): one with this phase's, one with the last
+// one's, one being filled for the next by direct global->LDS copies.
+// Bound: fp32 MFMA (2048 tokens, 16 heads, 192/128-wide: 280 us of products at the peak rate).
+// The first keys see every query, so their chain of tiles is the kernel's time when there
+// are no more workgroups than CUs; two pairs of waves halve it. Before (128 keys per workgroup,
+// each wave on every tile) / now, us, fp32: 2048 tokens, 16 heads 786 / 390, 32 heads x 4000 3100 / 2730;
+// 256 tokens, 4 heads of 48/32 51 / 22; bf16, 1000 tokens, 16 heads of 48/32 120 / 40.
+template <typename T, int DN, int DR, int DV>
+__global__ __launch_bounds__(256, DN == 128 ? 1 : 2) void dkdv_kernel(BwdParams P) {
+  constexpr int DQK = DN + DR, DKVH = DN + DV, DQK32 = round32(DQK), NDK = DQK32 / 32, NDV = DV / 32;
+  constexpr int BQ = 32, BK = 64, NS = 3, E = Elems16<T>::n;
   constexpr int PQ = lds_pitch<T>(DQK32), PO = lds_pitch<T>(DV);
   constexpr int QCH = DQK / E, OCH = DV / E;  // chunks per row
-  static_assert(QCH <= 64 && OCH <= 64 && BQ % 4 == 0 && BQ <= 32, "one copy instruction per row");
-  // two stages of [Q tile | dO tile | lse2 | delta], filled by direct global->LDS copies
-  // while the other stage is consumed (no registers held for the staging)
-  __shared__ __attribute__((aligned(16))) T sQb[2][BQ * PQ];
-  __shared__ __attribute__((aligned(16))) T sOb[2][BQ * PO];
-  __shared__ __attribute__((aligned(16))) float sLD[2][2 * BQ];
+  static_assert(QCH <= 64 && OCH <= 64, "one copy instruction per row");
+  constexpr int TQ = BQ * PQ, TO = BQ * PO;
+  __shared__ __attribute__((aligned(16))) T sm[NS * (TQ + TO)];  // Q slots, then dO slots
+  T* const sOm = sm + NS * TQ;
+  __shared__ __attribute__((aligned(16))) float sLD[NS][2 * BQ];
 
   const T* __restrict__ q = (const T*)P.q;
   const T* __restrict__ kpe = (const T*)P.k_pe;
@@ -47,16 +57,18 @@ __global__ __launch_bounds__(64 * WPH) void dkdv_kernel(BwdParams P) {
   heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_blocks, H * gridDim.y, bh, kb);
   const int b = bh / H, h = bh % H;
 
-  const int tid = threadIdx.x, wave = tid >> 6, l = tid & 63, n = l & 31, g = l >> 5;
-  const int k0 = kb * BK + wave * 32;  // first key of this wave
+  const int tid = threadIdx.x, l = tid & 63, n = l & 31, g = l >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;
+  const int kw = wave & 1, qw = wave >> 1;
+  const int k0 = kb * BK + kw * 32;  // first key of this wave
   const int my_k = k0 + n;
 
-  // zero the padding columns [DQK, DQK32) of both stages once: transposing reads of Q^T
+  // zero the padding columns [DQK, DQK32) of every slot once: transposing reads of Q^T
   // blocks touch them
   if (DQK32 > DQK)
-    for (int i = tid; i < 2 * BQ * (DQK32 - DQK); i += 64 * WPH) {
+    for (int i = tid; i < NS * BQ * (DQK32 - DQK); i += 256) {
       const int st = i / (BQ * (DQK32 - DQK)), j = i % (BQ * (DQK32 - DQK));
-      sQb[st][(j / (DQK32 - DQK)) * PQ + DQK + j % (DQK32 - DQK)] = to_elem<T>(0.f);
+      sm[st * TQ + (j / (DQK32 - DQK)) * PQ + DQK + j % (DQK32 - DQK)] = to_elem<T>(0.f);
     }
 
   // this lane's key and value rows (B operands of S = Q K^T and dP = dO V^T)
@@ -82,100 +94,135 @@ __global__ __launch_bounds__(64 * WPH) void dkdv_kernel(BwdParams P) {
     }
   }
 
-  f32x16 dk[DQK32 / 32], dv[DV / 32];
+  f32x16 dk[NDK], dv[NDV];
 #pragma unroll
-  for (int i = 0; i < DQK32 / 32; ++i)
+  for (int i = 0; i < NDK; ++i) dk[i] = f32x16{};
 #pragma unroll
-    for (int r = 0; r < 16; ++r) dk[i][r] = 0.f;
-#pragma unroll
-  for (int i = 0; i < DV / 32; ++i)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) dv[i][r] = 0.f;
+  for (int i = 0; i < NDV; ++i) dv[i] = f32x16{};
 
-  // Stage st <- query tile qt: row r of the 2*BQ Q and dO rows is one copy instruction
-  // of wave r % WPH (lane l copies chunk l of the row); rows past S are zero-filled by
-  // LDS stores. lse2 and delta rows are padded to S_pad (a multiple of 64 >= S), so their
-  // BQ entries are copied whole by the last wave: lanes [0, BQ/4) lse2, [BQ/4, BQ/2) delta.
-  const size_t ld_row = (size_t)(b * H + h) * P.S_pad;
-  auto fill = [&](int st, int qt) {
-    for (int r = wave; r < 2 * BQ; r += WPH) {
-      const bool isq = r < BQ;
-      const int row = isq ? r : r - BQ, qi = qt + row;
-      T* dst = isq ? &sQb[st][row * PQ] : &sOb[st][row * PO];
-      if (l < (isq ? QCH : OCH)) {
-        if (qi < S) {
-          const size_t base = (size_t)(b * S + qi) * H + h;
-          g2lds16(isq ? q + base * DQK + l * E : dout + base * DV + l * E, dst);
-        } else {
-          *reinterpret_cast<chunk16*>(dst + l * E) = zero_chunk();
-        }
+  const int qt_begin = P.causal ? kb * BK : 0;
+  const int nt = (S - qt_begin + BQ - 1) / BQ;
+  // Slot <- tile j: wave w copies rows 8 w .. of Q and of dO, one instruction per row (lane l
+  // chunk l); rows past S copy row S - 1 (masked below). lse2 and delta rows are padded to S_pad
+  // (a multiple of 64 >= S): their BQ entries are copied whole by the last wave.
+  const size_t hrow0 = (size_t)(b * S) * H + h, ld_row = (size_t)bh * P.S_pad;
+  auto fill = [&](int st, int j) {
+    const int qt = qt_begin + j * BQ;
+    if (l < QCH)
+#pragma unroll
+      for (int i = 0; i < BQ / 4; ++i) {
+        const int r = wave * (BQ / 4) + i;
+        g2lds16_so(q + (hrow0 + (size_t)min(qt + r, S - 1) * H) * DQK, 16u * l, sm + st * TQ + r * PQ);
       }
-    }
-    if (wave == WPH - 1 && l < BQ / 2) {
+    if (l < OCH)
+#pragma unroll
+      for (int i = 0; i < BQ / 4; ++i) {
+        const int r = wave * (BQ / 4) + i;
+        g2lds16_so(dout + (hrow0 + (size_t)min(qt + r, S - 1) * H) * DV, 16u * l, sOm + st * TO + r * PO);
+      }
+    if (wave == 3 && l < BQ / 2) {
       const float* src = l < BQ / 4 ? P.lse2 + ld_row + qt + 4 * l : P.delta + ld_row + qt + 4 * (l - BQ / 4);
       g2lds16(src, &sLD[st][0]);
     }
   };
 
-  const int qt_begin = P.causal ? (kb * BK) / BQ * BQ : 0;
-  fill(0, qt_begin);
-  int st = 0;
-  for (int qt = qt_begin; qt < S; qt += BQ, st ^= 1) {
-    wait_vmem();      // this wave's copies of tile qt have landed
-    __syncthreads();  // every wave's copies and zero stores of stage st are visible; stage st^1
-                      // is no longer read
-    if (qt + BQ < S) fill(st ^ 1, qt + BQ);
-    const T* sQ = sQb[st];
-    const T* sO = sOb[st];
-    const float* sL = sLD[st];
-    const float* sD = sLD[st] + BQ;
-
-    const bool active = k0 < S && (!P.causal || qt + BQ - 1 >= k0);
-    if (!active) continue;
+  // A of tile j (slot st): P in sa and dZ in dp, rows = queries (r/4)*8 + g*4 + r%4, column = my key
+  f32x16 sa, dp;
+  auto half_a = [&](int st, int j) {
+    const T *sQ = sm + st * TQ, *sO = sOm + st * TO;
+    const float *sL = sLD[st], *sD = sLD[st] + BQ;
+    const int qt = qt_begin + j * BQ;
+    sa = f32x16{};
+    dp = f32x16{};
+#pragma unroll
+    for (int ks = 0; ks < DQK / 16; ++ks) mma(sa, lds_frag<T>(sQ + n * PQ + ks * 16 + 8 * g), kf[ks]);
+#pragma unroll
+    for (int ks = 0; ks < DV / 16; ++ks) mma(dp, lds_frag<T>(sO + n * PO + ks * 16 + 8 * g), vf[ks]);
     const bool need_mask = (P.causal && qt < k0 + 31) || (qt + BQ > S);
-
-    f32x16 sa[BQ / 32], dp[BQ / 32];
 #pragma unroll
-    for (int qb = 0; qb < BQ / 32; ++qb) {
+    for (int rr = 0; rr < 4; ++rr) {
+      const int qrow = rr * 8 + g * 4;
+      const f32x4 lq = *reinterpret_cast<const f32x4*>(sL + qrow);
+      const f32x4 dq = *reinterpret_cast<const f32x4*>(sD + qrow);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { sa[qb][r] = 0.f; dp[qb][r] = 0.f; }
-#pragma unroll
-      for (int ks = 0; ks < DQK / 16; ++ks)
-        mma(sa[qb], lds_frag<T>(sQ + (qb * 32 + n) * PQ + ks * 16 + 8 * g), kf[ks]);
-#pragma unroll
-      for (int ks = 0; ks < DV / 16; ++ks)
-        mma(dp[qb], lds_frag<T>(sO + (qb * 32 + n) * PO + ks * 16 + 8 * g), vf[ks]);
-    }
-    // P and dZ (in place): rows = queries qt + qb*32 + (r/4)*8 + g*4 + r%4, column = my key
-#pragma unroll
-    for (int qb = 0; qb < BQ / 32; ++qb)
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        const int qrow = qb * 32 + rr * 8 + g * 4;
-        const f32x4 lq = *reinterpret_cast<const f32x4*>(sL + qrow);
-        const f32x4 dq = *reinterpret_cast<const f32x4*>(sD + qrow);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = rr * 4 + e;
-          float p = fast_exp2(sa[qb][r] * P.scale_log2 - lq[e]);
-          if (need_mask) {
-            const int qi = qt + qrow + e;
-            if (qi >= S || (P.causal && my_k > qi)) p = 0.f;
-          }
-          sa[qb][r] = p;
-          dp[qb][r] = p * (dp[qb][r] - dq[e]);
+      for (int e = 0; e < 4; ++e) {
+        const int r = rr * 4 + e;
+        float p = fast_exp2(sa[r] * P.scale_log2 - lq[e]);
+        if (need_mask) {
+          const int qi = qt + qrow + e;
+          if (qi >= S || (P.causal && my_k > qi)) p = 0.f;
         }
+        sa[r] = p;
+        dp[r] = p * (dp[r] - dq[e]);
       }
+    }
+  };
+  auto half_c = [&](int st) {
+    const T *sQ = sm + st * TQ, *sO = sOm + st * TO;
 #pragma unroll
     for (int kk = 0; kk < BQ / 16; ++kk) {
-      const frag_t<T> pf = acc_to_frag<T>(sa[kk >> 1], kk & 1);
-      const frag_t<T> zf = acc_to_frag<T>(dp[kk >> 1], kk & 1);
+      const frag_t<T> pf = acc_to_frag<T>(sa, kk), zf = acc_to_frag<T>(dp, kk);
       const int ra = kk * 16 + 4 * g;
 #pragma unroll
-      for (int db = 0; db < DV / 32; ++db) mma(dv[db], TrRead<T>::get(sO, PO, ra, ra + 8, db * 32), pf);
+      for (int db = 0; db < NDV; ++db) mma(dv[db], TrRead<T>::get(sO, PO, ra, ra + 8, db * 32), pf);
 #pragma unroll
-      for (int db = 0; db < DQK32 / 32; ++db) mma(dk[db], TrRead<T>::get(sQ, PQ, ra, ra + 8, db * 32), zf);
+      for (int db = 0; db < NDK; ++db) mma(dk[db], TrRead<T>::get(sQ, PQ, ra, ra + 8, db * 32), zf);
     }
+  };
+  // tiles that this wave works on at all (wave-uniform): its keys exist and some query sees them
+  auto active = [&](int j) { return k0 < S && (!P.causal || qt_begin + j * BQ + BQ - 1 >= k0); };
+
+  // start of phase p: tile p is there, tile p + 1 on its way into the slot of tile p - 2
+  auto phase = [&](int p) {
+    wait_vmem();      // this wave's copies of tile p have landed
+    __syncthreads();  // everyone's; tile p - 2 is no longer read
+    if (p + 1 < nt) fill((p + 1) % NS, p + 1);
+  };
+  fill(0, 0);
+  if (qw) phase(0);
+  for (int p = qw; p < nt; p += 2) {
+    const bool on = active(p);
+    phase(p);
+    if (on) half_a(p % NS, p);
+    phase(p + 1);
+    if (on) half_c(p % NS);
+  }
+  if ((nt & 1) == qw) phase(nt);  // every wave goes through phases 0 .. nt
+
+  // the first wave of a pair takes the other's dK and finishes it, the second the first's dV
+  // (even + odd tiles)
+  __syncthreads();
+  static_assert(2 * (NDK + NDV) * 4096 <= (int)sizeof(T) * NS * (TQ + TO), "partials fit the slots");
+  // dK partials of both key halves, then dV's, 4 KB per 32 x 32 block
+  auto block = [&](int i) { return (float*)sm + i * 1024; };
+  auto put_x = [&](int i, const f32x16& a) {
+    float* x = block(i) + l * 4;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) *reinterpret_cast<f32x4*>(x + r * 256) = f32x4{a[4 * r], a[4 * r + 1], a[4 * r + 2], a[4 * r + 3]};
+  };
+  auto add_x = [&](int i, f32x16& a) {
+    const float* x = block(i) + l * 4;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(x + r * 256);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[4 * r + e] += v[e];
+    }
+  };
+  if (qw == 0) {
+#pragma unroll
+    for (int i = 0; i < NDV; ++i) put_x(2 * NDK + kw * NDV + i, dv[i]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < NDK; ++i) put_x(kw * NDK + i, dk[i]);
+  }
+  __syncthreads();
+  if (qw == 0) {
+#pragma unroll
+    for (int i = 0; i < NDK; ++i) add_x(kw * NDK + i, dk[i]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < NDV; ++i) add_x(2 * NDK + kw * NDV + i, dv[i]);
   }
 
   if (my_k >= S) return;
@@ -193,35 +240,36 @@ __global__ __launch_bounds__(64 * WPH) void dkdv_kernel(BwdParams P) {
       *reinterpret_cast<typename FragOf<T>::half*>(dkvl + col) = lo;
     }
   };
+  if (qw == 0) {
 #pragma unroll
-  for (int db = 0; db < DQK32 / 32; ++db)
+    for (int db = 0; db < NDK; ++db)
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      const int d = db * 32 + rr * 8 + g * 4;
-      const float a0 = dk[db][4 * rr] * P.scale, a1 = dk[db][4 * rr + 1] * P.scale;
-      const float a2 = dk[db][4 * rr + 2] * P.scale, a3 = dk[db][4 * rr + 3] * P.scale;
-      if (d < DN) {
-        put4(d, a0, a1, a2, a3);
-      } else if (d < DQK) {
-        f32x4 v = {a0, a1, a2, a3};
-        *reinterpret_cast<f32x4*>(dper + (d - DN)) = v;
+      for (int rr = 0; rr < 4; ++rr) {
+        const int d = db * 32 + rr * 8 + g * 4;
+        const float a0 = dk[db][4 * rr] * P.scale, a1 = dk[db][4 * rr + 1] * P.scale;
+        const float a2 = dk[db][4 * rr + 2] * P.scale, a3 = dk[db][4 * rr + 3] * P.scale;
+        if (d < DN) {
+          put4(d, a0, a1, a2, a3);
+        } else if (d < DQK) {
+          f32x4 v = {a0, a1, a2, a3};
+          *reinterpret_cast<f32x4*>(dper + (d - DN)) = v;
+        }
       }
-    }
+  } else {
 #pragma unroll
-  for (int db = 0; db < DV / 32; ++db)
+    for (int db = 0; db < NDV; ++db)
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr)
-      put4(DN + db * 32 + rr * 8 + g * 4, dv[db][4 * rr], dv[db][4 * rr + 1], dv[db][4 * rr + 2], dv[db][4 * rr + 3]);
+      for (int rr = 0; rr < 4; ++rr)
+        put4(DN + db * 32 + rr * 8 + g * 4, dv[db][4 * rr], dv[db][4 * rr + 1], dv[db][4 * rr + 2], dv[db][4 * rr + 3]);
+  }
 }
 
 }  // namespace
 
 template <typename T, int DN, int DR, int DV>
 hipError_t launch_dkdv_generic(BwdParams P, int B, hipStream_t st) {
-  using Tl = BwdTiles<T>;
-  constexpr int BK = 32 * Tl::WPH_KV;
-  P.n_blocks = (P.S + BK - 1) / BK;
-  dkdv_kernel<T, DN, DR, DV, Tl::BQ, Tl::WPH_KV><<<dim3(P.n_blocks * P.H, B), 64 * Tl::WPH_KV, 0, st>>>(P);
+  P.n_blocks = (P.S + 63) / 64;
+  dkdv_kernel<T, DN, DR, DV><<<dim3(P.n_blocks * P.H, B), 256, 0, st>>>(P);
   return hipGetLastError();
 }
 

@@ -76,10 +76,5 @@ __host__ __device__ inline int ds_tile_keys(int T, int causal, int t) { return c
 // heads: 1000 74 / 90. 16 heads, no mask: 1000 51 / 38, 1900 105 / 112.
 constexpr int kDkdvSplitMaxCausal = 2304, kDkdvSplitMaxFull = 1280;
 
-template <typename T> struct BwdTiles;
-template <> struct BwdTiles<bf16> { static constexpr int BQ = 32, BC = 64, WPH_KV = 4, WPH_Q = 4; };
-template <> struct BwdTiles<float> { static constexpr int BQ = 32, BC = 32, WPH_KV = 4, WPH_Q = 4; };
-
-
 }  // namespace bwd
 }  // namespace laga

@@ -951,8 +951,17 @@ hipError_t launch_finish(const FinishParams& f, hipStream_t st) {
     }
   } else {
     using G = GemmCfg<T>;
-    gemm_kernel<T, float, false, false, G::BM, G::BN, G::BK><<<grid_tiles(M, N, G::BM, G::BN), kThreads, 0, st>>>(
-        dkv, w, f.dc, M, N, K, K, K, N, K, 0);
+    // dc's contraction in the plan's splits here too: one 64 x 64 tile per CU leaves the CUs
+    // waiting on its loads (2048 tokens, 16 heads: 141 us in one range, 94 in four)
+    const int k_chunk = (K / plan.splits + G::BK - 1) / G::BK * G::BK;
+    nz = (K + k_chunk - 1) / k_chunk;
+    gemm_kernel<T, float, false, false, G::BM, G::BN, G::BK><<<dim3(grid_tiles(M, N, G::BM, G::BN), 1, nz), kThreads, 0,
+                                                               st>>>(dkv, w, nz == 1 ? f.dc : dc_part, M, N, K, K, K, N,
+                                                                     k_chunk, sdc);
+    if (!plan.pair && nz > 1) {
+      split_reduce_kernel<<<(unsigned)((sdc / 4 + 255) / 256), 256, 0, st>>>(dc_part, f.dc, sdc / 4, nz, sdc);
+      nz = 1;
+    }
     gemm_kernel<T, float, true, true, G::BM, G::BN, G::BK><<<dim3(grid_tiles(N, K, G::BM, G::BN), 1, nw), kThreads, 0,
                                                              st>>>(c, dkv, nw == 1 ? f.dw : dw_part, N, K, M, N, K, K,
                                                                    split, sdw);
