@@ -1,4 +1,4 @@
-"""The bf16 GEMMs behind laga_reconstruct_kv, laga_attn_bwd's dc_kv / dW and laga_out_proj_*
+"""The GEMMs behind laga_reconstruct_kv, laga_attn_bwd's dc_kv / dW and laga_out_proj_*
 at the edges of their tile shapes and of the rules that choose them: partial row tiles,
 contractions that end inside a 32-index stage (odd token counts; d_model and F at 16 mod 32),
 single rows, and both sides of each rule. The reference is the product in float64 of the
@@ -23,6 +23,37 @@ def check(got, a, b, where):
 def randn(gen, *shape):
     import torch
     return torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+
+
+# fp32: 16-wide contraction steps loaded four ahead (2, 4, 6, 64 of them) and partial row tiles;
+# fp32 accumulation of K products, 2^-24 relative per addition in the worst case (and one more
+# for the sum of split ranges)
+@pytest.mark.parametrize("T,H,d_c", [(1, 1, 32), (63, 2, 64), (65, 1, 96), (130, 3, 1024)])
+def test_reconstruct_fp32(T, H, d_c):
+    import torch
+    import paper_2607_17644_amd as L
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    c = torch.randn(1, T, d_c, generator=gen, device="cuda")
+    w = torch.randn(d_c, H * 256, generator=gen, device="cuda")
+    kv = L.laga_reconstruct_kv(L.Problem(1, T, H, d_c, 128, 64, 128, 0.07, dtype=L.DTYPE_FP32), c, w)
+    a, b = c[0].double(), w.double()
+    assert ((kv.double().reshape(T, -1) - a @ b).abs() <= (d_c + 1) * 2.0 ** -24 * (a.abs() @ b.abs())).all()
+
+
+# fp32 weight gradient of W_o: the contraction over the tokens ends inside a step and inside
+# the four steps in flight (1, 15, 17, 65 and 600 tokens, the last in two ranges)
+@pytest.mark.parametrize("T", [1, 15, 17, 65, 600])
+def test_out_proj_fp32(T):
+    import torch
+    import paper_2607_17644_amd as L
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    p = L.OutProj(T, 5, 16, 144, dtype=L.DTYPE_FP32)
+    out, w, dy = (torch.randn(s, generator=gen, device="cuda") for s in ((T, 5, 16), (80, 144), (T, 144)))
+    y = L.laga_out_proj_fwd(p, out, w)
+    d_out, dw = L.laga_out_proj_bwd(p, out, w, dy)
+    o = out.reshape(T, 80).double()
+    for got, a, b in ((y, o, w.double()), (d_out.reshape(T, 80), dy.double(), w.double().t()), (dw, o.t(), dy.double())):
+        assert ((got.double() - a @ b).abs() <= (a.shape[1] + 1) * 2.0 ** -24 * (a.abs() @ b.abs())).all()
 
 
 # N = 16 * 256: 128 x 128 tiles below 2049 rows, one round of whole tiles at 4096, partial row
