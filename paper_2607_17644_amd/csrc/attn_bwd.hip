@@ -431,9 +431,9 @@ __global__ __launch_bounds__(256, 1) void dkdv32_kernel(BwdParams P) {
       lds_barrier();
       fill((j + 2) % NS, tile_q(j + 2));
     } else {  // three slots hold the tiles of this step, the previous and the next one
-      // younger than the awaited copies are only the two dS^T stores of step j - 1 (a wave may
-      // have none there on the diagonal, j = 1 and 2: then everything is awaited)
-      if (STORE_DS && j > 2) wait_vmem_le<2>();
+      // younger than the awaited copies are only the two dS^T stores of step j - 2, issued in
+      // step j - 1; where a wave may have issued none, everything is awaited
+      if (STORE_DS && dkdv_split_wait_counts(P.ds_T, k0, j)) wait_vmem_le<2>();
       else wait_vmem();
       lds_barrier();
       fill((j + 1) % NS, tile_q(j + 1));

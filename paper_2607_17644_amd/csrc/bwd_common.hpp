@@ -76,5 +76,13 @@ __host__ __device__ inline int ds_tile_keys(int T, int causal, int t) { return c
 // heads: 1000 74 / 90. 16 heads, no mask: 1000 51 / 38, 1900 105 / 112.
 constexpr int kDkdvSplitMaxCausal = 2304, kDkdvSplitMaxFull = 1280;
 
+// dkdv32_kernel with QS = 2 and the dS^T store: whether a wave (first key k0, T = ceil(S / 32)
+// tiles) is certain to have issued the two dS^T stores of step j - 2 after the copies that it
+// awaits at the start of step j, so that its wait may leave two operations in flight. Not
+// before step 3 (no store yet, or none on the diagonal), and never in a wave whose keys all lie
+// past the stored ones: without the mask and with an odd T that is the second half of the last
+// 64-key workgroup, which stores nothing at all and copies rows that the first half reads.
+__host__ __device__ constexpr bool dkdv_split_wait_counts(int T, int k0, int j) { return j > 2 && k0 < 32 * T; }
+
 }  // namespace bwd
 }  // namespace laga
