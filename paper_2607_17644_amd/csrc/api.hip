@@ -6,6 +6,7 @@
 #include <mutex>
 
 #include "laga.h"
+#include "gemm_plan.hpp"
 #include "kernels.hpp"
 #include "bwd_common.hpp"
 

@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "gemm_plan.hpp"
 #include "kernels.hpp"
 
 namespace laga {
@@ -222,8 +223,6 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(
 //     chunk c of k row r at c ^ (4 (r & 3)). A transposing read covers 4 consecutive
 //     k rows x 4 chunks per half-wave, which the XOR spreads over the four 64-byte
 //     quarters of the banks.
-constexpr int kGK = 32;  // contraction per stage
-
 // This lane's share of the copies of one operand tile (ROWS / 16 instructions, wave w
 // of NWV issues w, w + NWV, ...).
 template <bool KS, int ROWS, int NWV = 4>
@@ -740,7 +739,7 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const float* __restri
 }
 
 template <typename T> struct GemmCfg;
-template <> struct GemmCfg<float> { static constexpr int BM = 64, BN = 64, BK = 16; };
+template <> struct GemmCfg<float> { static constexpr int BM = 64, BN = 64, BK = kFp32GK; };
 
 // The backward's last launch: dc and dW from their split partials (ascending splits) and
 // dk_pe[t, :] = sum over heads (ascending) of the per-head parts, 4 values per thread. One
@@ -777,9 +776,6 @@ __global__ __launch_bounds__(256) void finish_reduce_kernel(FinishArgs a) {
     reinterpret_cast<f32x4*>(a.dk_pe)[i] = s;
   }
 }
-
-inline int grid_tiles(int M, int N, int BM, int BN) { return ((M + BM - 1) / BM) * ((N + BN - 1) / BN); }
-constexpr int kCUs = 256;  // compute units of the gfx950 part (one large-tile workgroup each)
 
 // bf16 tile shapes of gemm_ring_kernel: "large" (the caller's BM x BN, 65536 outputs),
 // 256 x 128 (both eight waves, one workgroup per CU) and 128 x 128 (four waves, two
@@ -843,85 +839,6 @@ hipError_t launch_reconstruct(const T* c, const T* w, T* kv, int M, int N, int K
   return hipGetLastError();
 }
 
-int dw_split_tokens(int tokens) {
-  int s = 2048;
-  while (s > 512 && (tokens + s - 1) / s < 4) s /= 2;
-  return s;
-}
-size_t dw_split_count(int tokens) {
-  const int s = dw_split_tokens(tokens);
-  return (size_t)((tokens + s - 1) / s);
-}
-
-namespace {
-// dc's tiles: 128 x 128 (two workgroups per CU) while they fill the CUs no more than about
-// once, with the contraction split where they don't (at least 512 indices per split); beyond,
-// 128 x 512 (256 x 256 for d_c <= 256: the whole d_c side, so dKV is read once) over as many
-// splits as fit the CUs and the partials of dW (so that dc adds nothing to the workspace).
-// Measured (us with the reduction, 16 heads, d_c 512; 128 x 128 / 128 x 512, its splits in
-// brackets): 1000 tokens 20 (8) / 31 (16), 2048 27 (4) / 38 (8), 4096 43 (2) / 50 (8), 8192
-// 68 (1) / 76 (4), 10002 112 (1) / 96 (2), 16384 159 (1) / 135 (2).
-size_t dw_partial_elems(int tokens, int d_c, int K) {
-  return dw_split_count(tokens) > 1 ? dw_split_count(tokens) * (size_t)d_c * K : 0;
-}
-// dc and dW share a launch up to this many 128 x 128 workgroups (two per CU).
-constexpr int kPairMaxGroups = 2 * kCUs;
-bool dc_wide(int tokens, int d_c) { return grid_tiles(tokens, d_c, 128, 128) > kCUs + kCUs / 8; }
-// Partials that dc may have beside dW's (floats; 128 x 128 tiles, where one last launch sums
-// both). The sum of both stays within max(dW's, the splits of a 512-workgroup grid or of 128 x
-// 512 tiles, at least 256 indices each), so that every problem whose workspace fits the fixed
-// array of laga_attn_bwd_noalloc keeps fitting it.
-size_t dc_partial_room(int tokens, int d_c, int K) {
-  const bool aligned = tokens % 8 == 0;
-  const int tiles = !aligned    ? grid_tiles(tokens, d_c, 128, 128)
-                    : d_c > 256 ? grid_tiles(tokens, d_c, 128, 512)
-                                : grid_tiles(tokens, d_c, 256, 256);
-  const int want = aligned ? kCUs : 2 * kCUs, most = K >= 512 ? K / 256 : 1;
-  const int n = min((want + tiles - 1) / tiles, most);
-  const size_t cap = n > 1 ? (size_t)n * tokens * d_c : 0, dw = dw_partial_elems(tokens, d_c, K);
-  return cap > dw ? cap - dw : 0;
-}
-}  // namespace
-
-namespace {
-// Splits of dc's contraction, and whether dc and dW share a launch (gemm_pair.hip): when the
-// 128 x 128 tiles of both fit the chip at once and the workspace has room for the partials of
-// both (a quarter fewer splits of dc than wanted is a fair price); the last launch then sums
-// both. Otherwise dc's partials lie in the place of dW's and are summed right away, while they
-// are in cache (2048 tokens, 16 heads: left to the last launch 5 us slower). Measured, the
-// whole stage (us, apart / shared): 16 heads 100 tokens 26 / 17, 300 31 / 20, 1000 47 / 37, 8
-// heads 1000 36 / 23; half-width heads, 4 x 2000 68 / 59.
-struct DcPlan {
-  bool wide, pair;
-  int splits;
-};
-DcPlan dc_plan(int tokens, int d_c, int K) {
-  DcPlan p{};
-  p.wide = dc_wide(tokens, d_c);
-  const int tiles = !p.wide     ? grid_tiles(tokens, d_c, 128, 128)
-                    : d_c > 256 ? grid_tiles(tokens, d_c, 128, 512)
-                                : grid_tiles(tokens, d_c, 256, 256);
-  const size_t each = (size_t)tokens * d_c;
-  int n = min(kCUs / tiles, K >= 1024 ? K / 512 : 1);
-  if (p.wide) n = min(n, (int)(dw_partial_elems(tokens, d_c, K) / each));
-  p.splits = n < 1 ? 1 : n;
-  if (!p.wide) {
-    const int fit = min(p.splits, (int)(dc_partial_room(tokens, d_c, K) / each));
-    const int ns = p.splits == 1 || 4 * fit < 3 * p.splits ? p.splits : fit;
-    p.pair = (p.splits == 1 || 4 * fit >= 3 * p.splits) &&
-             tiles * ns + grid_tiles(d_c, K, 128, 128) * (int)dw_split_count(tokens) <= kPairMaxGroups;
-    if (p.pair) p.splits = ns;
-  }
-  return p;
-}
-}  // namespace
-
-size_t gemm_partial_elems(int tokens, int d_c, int K) {
-  const DcPlan p = dc_plan(tokens, d_c, K);
-  const size_t dw = dw_partial_elems(tokens, d_c, K), dc = p.splits > 1 ? (size_t)p.splits * tokens * d_c : 0;
-  return p.pair ? dw + dc : dw > dc ? dw : dc;
-}
-
 template <typename T>
 hipError_t launch_finish(const FinishParams& f, hipStream_t st) {
   // dc[tokens][d_c] = (dKV + dKV_lo)[tokens][ncol] @ W^T, W stored [d_c][ncol] (k-contiguous);
@@ -937,8 +854,9 @@ hipError_t launch_finish(const FinishParams& f, hipStream_t st) {
   int nz = 1;  // splits of dc
   if constexpr (sizeof(T) == 2) {
     const T* lo = (const T*)f.dkv_lo;
-    const int k_chunk = (K / plan.splits + kGK - 1) / kGK * kGK;
-    nz = (K + k_chunk - 1) / k_chunk;
+    const DcRanges r = dc_ranges(plan.splits, K, kGK);
+    const int k_chunk = r.chunk;
+    nz = r.n;
     float *dc = nz == 1 ? f.dc : dc_part, *dw = nw == 1 ? f.dw : dw_part;
     const int tdc = grid_tiles(M, N, 128, 128), tdw = grid_tiles(N, K, 128, 128);
     if (plan.pair) {
@@ -969,8 +887,9 @@ hipError_t launch_finish(const FinishParams& f, hipStream_t st) {
     using G = GemmCfg<T>;
     // dc's contraction in the plan's splits here too: one 64 x 64 tile per CU leaves the CUs
     // waiting on its loads (2048 tokens, 16 heads: 141 us in one range, 94 in four)
-    const int k_chunk = (K / plan.splits + G::BK - 1) / G::BK * G::BK;
-    nz = (K + k_chunk - 1) / k_chunk;
+    const DcRanges r = dc_ranges(plan.splits, K, G::BK);
+    const int k_chunk = r.chunk;
+    nz = r.n;
     gemm_kernel<T, float, false, false, G::BM, G::BN, G::BK><<<dim3(grid_tiles(M, N, G::BM, G::BN), 1, nz), kThreads, 0,
                                                                st>>>(dkv, w, nz == 1 ? f.dc : dc_part, M, N, K, K, K, N,
                                                                      k_chunk, sdc);

@@ -10,16 +10,6 @@ namespace laga {
 // multiple of this many queries, so query tiles can be fetched whole.
 constexpr int kRowPad = 64;
 
-// Tokens per split of the dW reduction over tokens: a function of the token count only
-// (never of the head count), so each dW column is bit-identical whatever head shard
-// computes it. 2048 for long sequences, down to 512 for short ones (enough workgroups).
-int dw_split_tokens(int tokens);
-size_t dw_split_count(int tokens);
-// Workspace of the split partials of dc_kv (its contraction, over the shard's heads x 256, is
-// split so that the launch has enough workgroups; dc_kv sums over heads, so no bit-identity
-// across head shards is asked of it) and of dW.
-size_t gemm_partial_elems(int tokens, int d_c, int K);
-
 template <typename T>
 hipError_t launch_reconstruct(const T* c, const T* w, T* kv, int M, int N, int K, hipStream_t st);
 // Last stage of the backward: dc_kv, dW and the head sum dk_pe.

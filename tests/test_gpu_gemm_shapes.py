@@ -118,6 +118,33 @@ def test_up_projection_backward(S, H, d_c):
     check(dw, c[0].double().t(), dkv, "dw_kv_b")
 
 
+# splits of dc_kv's contraction that do not divide it (31 of 16384 indices, 21 of 11776, 51 of
+# 34304): the ranges launched are no more than the partials that the workspace holds
+@pytest.mark.parametrize("dtype,S,H,d_c", [("fp32", 1000, 64, 64), ("fp32", 300, 46, 512), ("bf16", 100, 134, 544)])
+def test_dc_partials_stay_in_the_workspace(dtype, S, H, d_c):
+    import torch
+    import paper_2607_17644_amd as L
+    gen = torch.Generator(device="cuda").manual_seed(S)
+    bf = dtype == "bf16"
+    p = L.Problem(1, S, H, d_c, 128, 64, 128, 192 ** -0.5, dtype=L.DTYPE_BF16 if bf else L.DTYPE_FP32,
+                  dq_mode=L.DQ_RECOMPUTE)
+    c, kpe, q, dout = (torch.randn(s, generator=gen, device="cuda").to(p.torch_dtype)
+                       for s in ((1, S, d_c), (1, S, 64), (1, S, H, 192), (1, S, H, 128)))
+    w = (torch.randn(d_c, H * 256, generator=gen, device="cuda") * d_c ** -0.5).to(p.torch_dtype)
+    kv = L.laga_reconstruct_kv(p, c, w)
+    out, lse = L.laga_attn_fwd(p, q, c, kpe, w, kv)
+    need, guard = L.laga_workspace_bytes(p, L.OP_BWD), 4 * S * d_c + 4096
+    buf = torch.full((need + guard,), 0x5A, dtype=torch.uint8, device="cuda")
+    dq, dc, dkpe, dw = L.laga_attn_bwd(p, q, c, kpe, w, kv, out, lse, dout, workspace=buf[:need])
+    torch.cuda.synchronize()
+    assert bool((buf[need:] == 0x5A).all())
+    up = lambda n: (n + 255) // 256 * 256  # noqa: E731
+    o1, nb = 2 * up(4 * H * ((S + 63) // 64 * 64)), S * H * 256 * (2 if bf else 4)
+    dkv = sum(buf[o:o + nb].view(p.torch_dtype).double() for o in ((o1, o1 + up(nb)) if bf else (o1,))).reshape(S, -1)
+    for got, a, b in ((dc[0], dkv, w.double().t()), (dw, c[0].double().t(), dkv)):
+        assert ((got.double() - a @ b).abs() <= (a.shape[1] + 1) * 2.0 ** -24 * (a.abs() @ b.abs())).all()
+
+
 def test_tail_rows_do_not_leak():
     """Values far beyond the data's scale in the last token's row stay in that token's products:
     rows copied in the place of missing ones never reach a sum (33 tokens: one index in the
