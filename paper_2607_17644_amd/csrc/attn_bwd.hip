@@ -164,7 +164,7 @@ __global__ __launch_bounds__(256, 1) void dkdv32_kernel(BwdParams P) {
   const int S = P.S, H = P.H;
 
   int bh, kb;  // the first key blocks see the most queries
-  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_blocks, H * gridDim.y, bh, kb);
+  ordered_block(P.order, blockIdx.x, bh, kb);
   const int b = bh / H, h = bh % H;
 
   const int tid = threadIdx.x, l = tid & 63, n = l & 31, g = l >> 5;
@@ -703,7 +703,7 @@ hipError_t launch_dkdv32_short(BwdParams P, int B, hipStream_t st) {
 #endif
   constexpr int BK = 128 / kQS;
   P.n_blocks = (P.S + BK - 1) / BK;
-  const dim3 grid(P.n_blocks * P.H, B);
+  const dim3 grid = order_grid(P, B);
   if (P.w_t) {
     if (P.ds) dkdv32_kernel<128, 64, 128, true, true, kQS><<<grid, 256, 0, st>>>(P);
     else dkdv32_kernel<128, 64, 128, false, true, kQS><<<grid, 256, 0, st>>>(P);

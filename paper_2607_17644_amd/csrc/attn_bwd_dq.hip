@@ -46,7 +46,7 @@ __global__ __launch_bounds__(256, DN == 128 ? 1 : 2) void dq_kernel(BwdParams P)
   const int S = P.S, H = P.H;
 
   int bh, qblk;
-  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_blocks, H * gridDim.y, bh, qblk);
+  ordered_block(P.order, blockIdx.x, bh, qblk);
   qblk = P.n_blocks - 1 - qblk;
   const int b = bh / H, h = bh % H;
 
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(64 * NW, DN == 128 ? 1 : 2) void dq_rec_kernel(BwdP
   const int S = P.S, H = P.H;
 
   int bh, qblk;
-  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_blocks, H * gridDim.y, bh, qblk);
+  ordered_block(P.order, blockIdx.x, bh, qblk);
   qblk = P.n_blocks - 1 - qblk;
   const int b = bh / H, h = bh % H;
 
@@ -423,7 +423,7 @@ __global__ __launch_bounds__(64 * NW, 1) void dq_ds_kernel(BwdParams P) {
   const int S = P.S, H = P.H, TT = P.ds_T;
 
   int bh, qblk;
-  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_blocks, H * gridDim.y, bh, qblk);
+  ordered_block(P.order, blockIdx.x, bh, qblk);
   qblk = P.n_blocks - 1 - qblk;
   const int b = bh / H, h = bh % H;
 
@@ -564,7 +564,7 @@ __global__ __launch_bounds__(512, 1) void dq_ds_fused_kernel(BwdParams P) {
   const int S = P.S, H = P.H, TT = P.ds_T, dc = P.d_c;
 
   int bh, qblk;
-  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_blocks, H * gridDim.y, bh, qblk);
+  ordered_block(P.order, blockIdx.x, bh, qblk);
   qblk = P.n_blocks - 1 - qblk;
   const int b = bh / H, h = bh % H;
 
@@ -685,7 +685,7 @@ __global__ __launch_bounds__(256, 1) void dq_ds_fused2_kernel(BwdParams P) {
   const int S = P.S, H = P.H, TT = P.ds_T;
 
   int bh, qblk;
-  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_blocks, H * gridDim.y, bh, qblk);
+  ordered_block(P.order, blockIdx.x, bh, qblk);
   qblk = P.n_blocks - 1 - qblk;
   const int b = bh / H, h = bh % H;
 
@@ -866,19 +866,23 @@ hipError_t launch_bwd_dq(bwd::BwdParams P, int B, hipStream_t st) {
       if (P.w_t && P.d_c == kFusedMaxDc) {
         constexpr int TPW = 2;
         P.n_blocks = (P.ds_T + 4 * TPW - 1) / (4 * TPW);
-        dq_ds_fused2_kernel<DN, DR, DV, kFusedMaxDc, TPW><<<dim3(P.n_blocks * P.H, B), 256, 0, st>>>(P);
+        const dim3 grid = order_grid(P, B);
+        dq_ds_fused2_kernel<DN, DR, DV, kFusedMaxDc, TPW><<<grid, 256, 0, st>>>(P);
       } else if (P.w_t) {
         constexpr int WPH = 8;
         P.n_blocks = (P.ds_T + WPH - 1) / WPH;
-        dq_ds_fused_kernel<DN, DR, DV><<<dim3(P.n_blocks * P.H, B), 64 * WPH, 0, st>>>(P);
+        const dim3 grid = order_grid(P, B);
+        dq_ds_fused_kernel<DN, DR, DV><<<grid, 64 * WPH, 0, st>>>(P);
       } else {
         const int nb8 = (P.ds_T + 7) / 8;
         if ((long long)nb8 * P.H * B > kDqNarrowMaxGroups) {
           P.n_blocks = nb8;
-          dq_ds_kernel<DN, DR, DV, 8><<<dim3(P.n_blocks * P.H, B), 512, 0, st>>>(P);
+          const dim3 grid = order_grid(P, B);
+          dq_ds_kernel<DN, DR, DV, 8><<<grid, 512, 0, st>>>(P);
         } else {
           P.n_blocks = (P.ds_T + 3) / 4;
-          dq_ds_kernel<DN, DR, DV, 4><<<dim3(P.n_blocks * P.H, B), 256, 0, st>>>(P);
+          const dim3 grid = order_grid(P, B);
+          dq_ds_kernel<DN, DR, DV, 4><<<grid, 256, 0, st>>>(P);
         }
       }
       return hipGetLastError();
@@ -888,11 +892,13 @@ hipError_t launch_bwd_dq(bwd::BwdParams P, int B, hipStream_t st) {
     // no dS^T store: recompute S, P, dP and dS per key tile
     constexpr int RW = DQ_REC_WAVES;
     P.n_blocks = (P.S + 32 * RW - 1) / (32 * RW);
-    dq_rec_kernel<DN, DR, DV, RW><<<dim3(P.n_blocks * P.H, B), 64 * RW, 0, st>>>(P);
+    const dim3 grid = order_grid(P, B);
+    dq_rec_kernel<DN, DR, DV, RW><<<grid, 64 * RW, 0, st>>>(P);
     return hipGetLastError();
   }
   P.n_blocks = (P.S + 63) / 64;
-  dq_kernel<T, DN, DR, DV><<<dim3(P.n_blocks * P.H, B), 256, 0, st>>>(P);
+  const dim3 grid = order_grid(P, B);
+  dq_kernel<T, DN, DR, DV><<<grid, 256, 0, st>>>(P);
   return hipGetLastError();
 }
 

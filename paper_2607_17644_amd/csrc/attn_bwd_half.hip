@@ -49,7 +49,7 @@ __global__ __launch_bounds__(256, 2) void dkdv_half_kernel(BwdParams P) {
   const int S = P.S, H = P.H;
 
   int bh, kb;  // the first key blocks see the most queries
-  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_blocks, H * gridDim.y, bh, kb);
+  ordered_block(P.order, blockIdx.x, bh, kb);
   const int b = bh / H, h = bh % H;
 
   const int l = threadIdx.x & 63, n = l & 31, g = l >> 5;
@@ -270,7 +270,8 @@ __global__ __launch_bounds__(256, 2) void dkdv_half_kernel(BwdParams P) {
 
 hipError_t launch_dkdv_half(BwdParams P, int B, hipStream_t st) {
   P.n_blocks = (P.S + 127) / 128;
-  dkdv_half_kernel<64, 32, 64><<<dim3(P.n_blocks * P.H, B), 256, 0, st>>>(P);
+  const dim3 grid = order_grid(P, B);
+  dkdv_half_kernel<64, 32, 64><<<grid, 256, 0, st>>>(P);
   return hipGetLastError();
 }
 

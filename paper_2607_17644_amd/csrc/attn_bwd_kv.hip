@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256, DN == 128 ? 1 : 2) void dkdv_kernel(BwdParams 
   const int S = P.S, H = P.H;
 
   int bh, kb;  // the first key blocks see the most queries
-  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_blocks, H * gridDim.y, bh, kb);
+  ordered_block(P.order, blockIdx.x, bh, kb);
   const int b = bh / H, h = bh % H;
 
   const int tid = threadIdx.x, l = tid & 63, n = l & 31, g = l >> 5;
@@ -269,7 +269,8 @@ __global__ __launch_bounds__(256, DN == 128 ? 1 : 2) void dkdv_kernel(BwdParams 
 template <typename T, int DN, int DR, int DV>
 hipError_t launch_dkdv_generic(BwdParams P, int B, hipStream_t st) {
   P.n_blocks = (P.S + 63) / 64;
-  dkdv_kernel<T, DN, DR, DV><<<dim3(P.n_blocks * P.H, B), 256, 0, st>>>(P);
+  const dim3 grid = order_grid(P, B);
+  dkdv_kernel<T, DN, DR, DV><<<grid, 256, 0, st>>>(P);
   return hipGetLastError();
 }
 

@@ -55,6 +55,7 @@ struct FwdParams {
   void* out;
   float* lse;
   int S, H, n_qblocks, n_hgroups;
+  BlockOrder order;
   float scale_log2;  // softmax_scale * log2(e)
   int causal;
 };
@@ -159,9 +160,9 @@ void attn_fwd_kernel(FwdParams P) {
   const T* __restrict__ kv = (const T*)P.kv;
   const int S = P.S, H = P.H;
 
-  // heavy-first, head-major ordering; each XCD gets a contiguous range of heads
+  // the last query blocks see the most keys
   int hgb, qb;
-  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_qblocks, P.n_hgroups * gridDim.y, hgb, qb);
+  ordered_block(P.order, blockIdx.x, hgb, qb);
   qb = P.n_qblocks - 1 - qb;
   const int b = hgb / P.n_hgroups;
   const int h0 = (hgb % P.n_hgroups) * G;
@@ -300,7 +301,7 @@ __global__ __launch_bounds__(64 * WPH) void attn_fwd_ring_kernel(FwdParams P) {
   const int S = P.S, H = P.H;
 
   int bhg, qb;
-  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_qblocks, P.n_hgroups * gridDim.y, bhg, qb);
+  ordered_block(P.order, blockIdx.x, bhg, qb);
   qb = P.n_qblocks - 1 - qb;
   const int b = bhg / P.n_hgroups, h0 = (bhg % P.n_hgroups) * G;
 
@@ -496,6 +497,7 @@ struct FwdFusedParams {
   void* out;
   float* lse;
   int S, H, d_c, n_qblocks;
+  BlockOrder order;
   float scale_log2;
   int causal;
 };
@@ -549,7 +551,7 @@ __global__ __launch_bounds__(64 * WPH) void attn_fwd_fused_kernel(FwdFusedParams
   const int S = P.S, H = P.H, dc = P.d_c;
 
   int bh, qb;
-  heavy_first(blockIdx.x + gridDim.x * blockIdx.y, P.n_qblocks, H * gridDim.y, bh, qb);
+  ordered_block(P.order, blockIdx.x, bh, qb);
   qb = P.n_qblocks - 1 - qb;
   const int b = bh / H, h = bh % H;
 
@@ -722,6 +724,13 @@ __global__ __launch_bounds__(256) void frag_w_kernel(const T* __restrict__ w, T*
   wf[i] = w[(size_t)k * N + col];
 }
 
+// Launch grid of P.n_qblocks blocks for each of `heads`, in the order that it leaves in P.
+template <typename Params>
+dim3 order_grid(Params& P, int heads) {
+  P.order = block_order(P.n_qblocks, heads, P.causal);
+  return dim3(heads * P.n_qblocks);
+}
+
 template <typename T, int DN, int DR, int DV> struct FwdTiles;
 template <int DN, int DR, int DV> struct FwdTiles<bf16, DN, DR, DV> {
   static constexpr int BC = 64, WPH = 4, G = 1;
@@ -753,7 +762,6 @@ hipError_t launch_attn_fwd(const AttnFwdArgs& a, hipStream_t st) {
   P.n_hgroups = (a.H + Tl::G - 1) / Tl::G;
   P.scale_log2 = a.scale * 1.4426950408889634f;
   P.causal = a.causal;
-  dim3 grid(P.n_qblocks * P.n_hgroups, a.B, 1);
   if constexpr (sizeof(T) == 2 && DN >= 64 && Tl::G == 1) {
     // 8 waves: 256 queries of one head per workgroup, which halves the K/V tile
     // traffic of 4 waves (measured 8 % faster at S = 16384); 4 waves when 8 would leave
@@ -764,7 +772,8 @@ hipError_t launch_attn_fwd(const AttnFwdArgs& a, hipStream_t st) {
       constexpr int RW = decltype(rw)::value, RG = kFwdRingHeads, RBR = 32 * RW / RG;
       P.n_qblocks = (a.S + RBR - 1) / RBR;
       P.n_hgroups = (a.H + RG - 1) / RG;
-      attn_fwd_ring_kernel<DN, DR, DV, Tl::BC, RW, RG><<<dim3(P.n_qblocks * P.n_hgroups, a.B, 1), 64 * RW, 0, st>>>(P);
+      const dim3 grid = order_grid(P, a.B * P.n_hgroups);
+      attn_fwd_ring_kernel<DN, DR, DV, Tl::BC, RW, RG><<<grid, 64 * RW, 0, st>>>(P);
     };
     if constexpr (DN == 128) {
       if ((long long)((a.S + 255) / 256) * P.n_hgroups * a.B >= kFwdFillGroups) ring(std::integral_constant<int, 8>{});
@@ -774,6 +783,7 @@ hipError_t launch_attn_fwd(const AttnFwdArgs& a, hipStream_t st) {
     }
   } else {
     using Cfg = FwdCfg<T, DN, DR, DV, Tl::BC, Tl::WPH, Tl::G, false>;
+    const dim3 grid = order_grid(P, a.B * P.n_hgroups);
     attn_fwd_kernel<T, DN, DR, DV, Tl::BC, Tl::WPH, Tl::G, false><<<grid, Cfg::NT, 0, st>>>(P);
   }
   return hipGetLastError();
@@ -795,7 +805,7 @@ hipError_t launch_attn_fwd_fused(const AttnFwdArgs& a, void* w_t_ws, hipStream_t
   P.S = a.S; P.H = a.H; P.d_c = a.d_c; P.n_qblocks = (a.S + BR - 1) / BR;
   P.scale_log2 = a.scale * 1.4426950408889634f;
   P.causal = a.causal;
-  dim3 grid(P.n_qblocks * a.H, a.B, 1);
+  const dim3 grid = order_grid(P, a.B * a.H);
   if (a.d_c == kFusedMaxDc)
     attn_fwd_fused_kernel<T, DN, DR, DV, Tl::BC, FW, kFusedMaxDc, kFusedMaxDc><<<grid, 64 * FW, 0, st>>>(P);
   else

@@ -35,6 +35,7 @@ struct BwdParams {
   void* dkv_lo;    // [B,S,H,DN+DV] bf16 low halves (bf16 only; else unused)
   float* dkpe_h;   // [B,S,H,DR] fp32
   int S, H, n_blocks;
+  BlockOrder order;  // of the n_blocks blocks of every head (order_grid)
   float scale, scale_log2;
   int causal;
   // dS^T store (bf16 path with 192/128-wide heads): written by the key-stationary
@@ -47,6 +48,12 @@ struct BwdParams {
   const void* w_t;
   int d_c;
 };
+
+// Launch grid of P.n_blocks blocks per head, in the order that it leaves in P.
+inline dim3 order_grid(BwdParams& P, int B) {
+  P.order = block_order(P.n_blocks, B * P.H, P.causal);
+  return dim3(P.order.heads * P.n_blocks);
+}
 
 // dS^T store layout: for every (b, h) and query tile t of 32 rows, the keys that tile
 // sees (32 (t + 1) with the causal mask, 32 T without) as rows of 32 bf16 values, one

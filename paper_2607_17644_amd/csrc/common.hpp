@@ -354,21 +354,40 @@ __device__ __forceinline__ int xcd_remap(int id, int n) {
   return (id % kXcd) * (n / kXcd) + id / kXcd;
 }
 
-// Workgroup id -> (head bh of BH = B * H, block blk of nblk), blocks in ascending order over
-// every head of the XCD that the id lands on. With the causal mask a head's blocks differ in
-// work; the caller numbers them heaviest first, so each XCD starts the heavy blocks of all
-// its heads before the light ones, which then fill the gaps at the end (longest job first).
-// Measured against one head after the other (16 heads): dK/dV at 64/32/64-wide heads,
-// 4 x 2000 tokens 136 -> 110 us; 2 x 5001 tokens: forward 303 -> 282 us, dK/dV 655 -> 632;
-// 16384 tokens: the step 5548 -> 5490 us; 128 heads x 4096 tokens: forward 831 -> 765 us.
-__device__ __forceinline__ void heavy_first(int id, int nblk, int BH, int& bh, int& blk) {
-  if (BH % 8 == 0) {  // each XCD (id % 8) keeps BH / 8 whole heads, for its L2
-    const int hp = BH / 8, i = id / 8;
-    bh = (id % 8) * hp + i % hp;
-    blk = i / hp;
-  } else {
-    bh = id % BH;
-    blk = id / BH;
+// Workgroup id -> (head bh of BH = B * H, block blk of nblk). Heads are taken in groups, and in a
+// group each XCD (id % 8, as the hardware deals ids) keeps whole heads, for its L2, and takes
+// their blocks in ascending order over all of them. With the causal mask a head's blocks
+// differ in work and the caller numbers them heaviest first, so the heavy blocks of a group
+// start before its light ones, which fill the gaps at its end (longest job first), and the
+// last group ends the launch so. A group has about kOrderMasked (kOrderFull without the mask)
+// workgroups per XCD: with fewer heads in it the heavy blocks of one head run alone at its
+// end, with more the heads' operands leave the L2 between two blocks of one head.
+// Measured (us; one head after the other / all heads of the XCD in one group / this). Causal:
+// forward, 128 heads x 8192 tokens 2651 / 2663 / 2515, 2 x 128 x 4096 1427 / 1512 / 1370, 64
+// x 4096 377 / 328 / 328, 2 x 16 x 5001 274 / 252 / 252; dK/dV, 128 x 8192 6243 / 6442 / 6076,
+// 64/32/64-wide 4 x 16 x 2000 122 / 108 / 107. No mask: forward, 128 x 4096 1291 / 1305 / 1216;
+// dK/dV there 2944 / 3214 / 2963; 64/32/64-wide, 64 x 4096 706 / 655 / 647. Groups of half the
+// size, causal: forward at 64/32/64, 64 x 8192 706 -> 730; of twice the size, no mask: forward
+// 128 x 4096 1305, causal as one group.
+constexpr int kOrderMasked = 256, kOrderFull = 128;
+struct BlockOrder {
+  int heads, group, ids;  // B * H; heads of a group (a multiple of 8 unless it is the only one); its workgroups
+};
+inline BlockOrder block_order(int nblk, int heads, int causal) {
+  const int per_xcd = ((causal ? kOrderMasked : kOrderFull) + nblk - 1) / nblk;
+  const int group = heads < 8 * per_xcd ? heads : 8 * per_xcd;
+  return {heads, group, group * nblk};
+}
+__host__ __device__ __forceinline__ void ordered_block(const BlockOrder& o, unsigned id, int& bh, int& blk) {
+  const unsigned grp = id / o.ids, j = id - grp * o.ids, h0 = grp * o.group, left = o.heads - h0;
+  const unsigned hc = left < (unsigned)o.group ? left : o.group;
+  if (hc % 8 == 0) {
+    const unsigned c = hc / 8, i = j / 8;
+    bh = h0 + j % 8 * c + i % c;
+    blk = i / c;
+  } else {  // heads shared between XCDs
+    bh = h0 + j % hc;
+    blk = j / hc;
   }
 }
 
