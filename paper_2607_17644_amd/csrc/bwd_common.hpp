@@ -75,13 +75,21 @@ __host__ __device__ inline int ds_tile_keys(int T, int causal, int t) { return c
 // Sequence lengths below which dK/dV splits the queries over pairs of waves (dkdv32_kernel with
 // QS = 2; causal, full). A function of the sequence length and the mask alone, so that a
 // head's gradients do not depend on the heads or batch elements beside it; the lines are set
-// for the rank's share of 16 heads. A workgroup's first keys see every query, so with few
-// workgroups that chain is the kernel's time, and the split halves it; but its step takes
-// 13 % longer (copies one step ahead instead of two) and twice the workgroups pay 10 us of
-// first loads and last stores. Measured (us, QS = 1 / 2): 16 heads, causal: 300 tokens 22 /
-// 17, 1000 51 / 35, 2048 90 / 73, 3000 141 / 141; 32 heads: 1000 54 / 48, 2048 124 / 137; 64
-// heads: 1000 74 / 90. 16 heads, no mask: 1000 51 / 38, 1900 105 / 112.
-constexpr int kDkdvSplitMaxCausal = 2304, kDkdvSplitMaxFull = 1280;
+// for the rank's share of 16 heads, and more (batch x heads) pay for it. A workgroup's first
+// keys see every query, so with few workgroups that chain is the kernel's time, and the split
+// halves it; but its step takes 13 % longer (copies one step ahead instead of two) and twice
+// the workgroups pay 10 us of first loads and last stores. So every head count crosses
+// elsewhere, and the lines are a compromise, no crossing of any: with the mask 16 heads cross
+// between 2600 and 3000 tokens, 32 between 1000 and 1500, 64 between 300 and 600; without it,
+// where every workgroup is as long, where the 64-key ones stop fitting the 256 CUs at once (16
+// heads 1024 tokens, 8 heads 2048).
+// Measured (us, QS = 1 / 2), causal, 16, 32, 64, 128 heads: 300 tokens 23 / 17, 24 / 18, 25 /
+// 24, 31 / 40; 600 34 / 25, 35 / 28, 39 / 48, 71 / 93; 1000 50 / 35, 51 / 47, 74 / 88, 152 /
+// 182; 1500 68 / 49, 76 / 84, 138 / 162, 281 / 332; 2048 88 / 72, 117 / 133, 235 / 262, 468 /
+// 533; 2300 100 / 90, 145 / 161, 286 / 323, 569 / 653. No mask, 16, 32, 64 heads: 320 tokens
+// 23 / 18, 23 / 18, 24 / 32; 640 35 / 26, 36 / 44, 63 / 70; 8, 16, 32 heads: 1024 49 / 34, 51 /
+// 37, 60 / 69; 1200 57 / 38, 58 / 67, 105 / 102.
+constexpr int kDkdvSplitMaxCausal = 2304, kDkdvSplitMaxFull = 1025;
 
 // dkdv32_kernel with QS = 2 and the dS^T store: whether a wave (first key k0, T = ceil(S / 32)
 // tiles) is certain to have issued the two dS^T stores of step j - 2 after the copies that it
