@@ -89,7 +89,7 @@ __host__ __device__ inline int ds_tile_keys(int T, int causal, int t) { return c
 // 533; 2300 100 / 90, 145 / 161, 286 / 323, 569 / 653. No mask, 16, 32, 64 heads: 320 tokens
 // 23 / 18, 23 / 18, 24 / 32; 640 35 / 26, 36 / 44, 63 / 70; 8, 16, 32 heads: 1024 49 / 34, 51 /
 // 37, 60 / 69; 1200 57 / 38, 58 / 67, 105 / 102.
-constexpr int kDkdvSplitMaxCausal = 2304, kDkdvSplitMaxFull = 1025;
+constexpr int kDkdvSplitMaxCausal = 2304, kDkdvSplitMaxFull = 1280;
 
 // dkdv32_kernel with QS = 2 and the dS^T store: whether a wave (first key k0, T = ceil(S / 32)
 // tiles) is certain to have issued the two dS^T stores of step j - 2 after the copies that it
