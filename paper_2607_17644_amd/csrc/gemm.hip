@@ -777,18 +777,6 @@ __global__ __launch_bounds__(256) void finish_reduce_kernel(FinishArgs a) {
   }
 }
 
-// bf16 tile shapes of gemm_ring_kernel: "large" (the caller's BM x BN, 65536 outputs),
-// 256 x 128 (both eight waves, one workgroup per CU) and 128 x 128 (four waves, two
-// workgroups per CU). The larger a tile, the less operand traffic per product, but fewer
-// than kRingMinGroups workgroups leave CUs idle: the largest shape that gives them is
-// launched, else 128 x 128. Measured (us, large / 256 x 128 / 128 x 128, workgroups):
-//   dW, 16 heads, d_c 512:  1000 tokens 36 (64) / 23 (128) / 20 (256);  2048 tokens 38 (128) /
-//     30 (256) / 36 (512);  5001 tokens 59 (160) / 63 (320) / 69 (640);  16384 tokens 128 (256) /
-//     137 (512) / 192 (1024)
-//   y = out W_o (F = 16384, D = 7168):  300 tokens 306 (56) / 188 (112) / 136 (168);  1000 tokens
-//     309 (112) / 246 (224) / 328 (448);  2048 tokens 419 (224) / 563 (448) / 697 (896)
-constexpr int kRingMinGroups = 160;
-
 // C = A B over nz contraction ranges of k_chunk (C + z * M * N for range z); LBM x LBN: the large tile
 template <int LBM, int LBN, bool A_KS, bool B_KS, int SPLIT, typename TO>
 void launch_ring(const bf16* A, const bf16* B, const bf16* X2, TO* C, int M, int N, int K, int lda, int ldb, int ldc,
@@ -796,10 +784,11 @@ void launch_ring(const bf16* A, const bf16* B, const bf16* X2, TO* C, int M, int
   constexpr int NS = SPLIT ? 3 : 4;  // ring depth (LDS: at most 144 KB, 72 KB for 128 x 128)
   const long long stride = (long long)M * N;
   const int nl = grid_tiles(M, N, LBM, LBN), nm = grid_tiles(M, N, 256, 128);
-  if (nl * nz >= kRingMinGroups)
+  const RingTile tile = ring_tile(nl * nz, nm * nz);
+  if (tile == RingTile::kLarge)
     gemm_ring_kernel<LBM, LBN, 8, (LBM <= LBN ? 2 : 4), NS, A_KS, B_KS, SPLIT, TO><<<dim3(nl, 1, nz), 512, 0, st>>>(
         A, B, X2, C, M, N, K, lda, ldb, ldc, k_chunk, stride);
-  else if (nm * nz >= kRingMinGroups)
+  else if (tile == RingTile::kMiddle)
     gemm_ring_kernel<256, 128, 8, 4, NS, A_KS, B_KS, SPLIT, TO><<<dim3(nm, 1, nz), 512, 0, st>>>(
         A, B, X2, C, M, N, K, lda, ldb, ldc, k_chunk, stride);
   else

@@ -14,6 +14,26 @@ constexpr int kFp32GK = 16;  // contraction per step of the fp32 kernel
 
 inline int grid_tiles(int M, int N, int BM, int BN) { return ((M + BM - 1) / BM) * ((N + BN - 1) / BN); }
 
+// bf16 tile shapes of gemm_ring_kernel: "large" (the caller's BM x BN, 65536 outputs), "middle"
+// 256 x 128 (both eight waves, one workgroup per CU) and "small" 128 x 128 (four waves, two
+// workgroups per CU). The larger a tile, the less operand traffic per product, but fewer
+// than kRingMinGroups workgroups leave CUs idle: the largest shape that gives them is
+// launched, else the small one. A middle grid that does not fit the CUs at once takes a second
+// round for a few workgroups and loses to the large one, which needs no second.
+// Measured (us, large / middle / small, workgroups):
+//   dW, 16 heads, d_c 512:  1000 tokens 36 (64) / 23 (128) / 20 (256);  2048 tokens 38 (128) /
+//     30 (256) / 36 (512);  5001 tokens 59 (160) / 63 (320) / 69 (640);  16384 tokens 128 (256) /
+//     137 (512) / 192 (1024)
+//   y = out W_o (F = 16384, D = 7168):  300 tokens 306 (56) / 188 (112) / 136 (168);  1000 tokens
+//     309 (112) / 246 (224) / 328 (448);  2048 tokens 419 (224) / 563 (448) / 697 (896)
+//   kv, 16 heads, d_c 512:  2112 and 2304 tokens 22 (144) / 27 (288)
+constexpr int kRingMinGroups = 160;
+enum class RingTile { kLarge, kMiddle, kSmall };
+inline RingTile ring_tile(int large, int middle) {  // workgroups of each
+  if (large >= kRingMinGroups || middle > kCUs) return RingTile::kLarge;
+  return middle >= kRingMinGroups ? RingTile::kMiddle : RingTile::kSmall;
+}
+
 // Tokens per split of the dW reduction over tokens: a function of the token count only
 // (never of the head count), so each dW column is bit-identical whatever head shard
 // computes it. 2048 for long sequences, down to 512 for short ones (enough workgroups).

@@ -56,12 +56,13 @@ def test_out_proj_fp32(T):
         assert ((got.double() - a @ b).abs() <= (a.shape[1] + 1) * 2.0 ** -24 * (a.abs() @ b.abs())).all()
 
 
-# N = 16 * 256: 128 x 128 tiles below 2049 rows, one round of whole tiles at 4096, partial row
+# N = 16 * 256: 256 x 128 tiles up to 2048 rows, 256 x 256 above (2049, 2304), partial row
 # tiles in the persistent kernel (3841: one row in the last tile; 8000: uneven rounds), and
 # 5001 rows (the second round of the persistent kernel would be mostly idle); d_c 480, 96:
 # contractions too short for it
 @pytest.mark.parametrize("T,H,d_c", [(1, 1, 512), (127, 16, 512), (129, 16, 96), (2049, 16, 512), (3841, 16, 512),
-                                     (5001, 16, 512), (8000, 16, 512), (4097, 16, 480), (16383, 16, 512)])
+                                     (5001, 16, 512), (8000, 16, 512), (4097, 16, 480), (16383, 16, 512),
+                                     (2047, 16, 512), (2304, 16, 512)])
 def test_reconstruct(T, H, d_c):
     import torch
     import paper_2607_17644_amd as L
