@@ -267,33 +267,58 @@ __global__ __launch_bounds__(256, 1) void dkdv32_kernel(BwdParams P) {
     // one coalesced 1 KB read per wave
     const T* wt = (const T*)P.w_t + (size_t)h * (DKVH / 32) * (dc / 16) * 512 + l * 8;
     const T* cr = (const T*)P.c_kv + krow * dc + 8 * g;
-    constexpr int NB = DKVH / 32;
+    // With QS = 2 the two waves of the same keys rebuild half of the columns each (K_nope, V) and
+    // hand their fragments over in LDS. Rebuilt whole in both, the 64-key workgroups did twice
+    // the rebuild of the 128-key ones (us, both / halves / unsplit): 32 heads x 2048 tokens 213 /
+    // 169 / 155, 32 x 921 85 / 65 / 70, 16 x 2048 114 / 94 / 116, 16 x 1000 58 / 46 / 74.
+    constexpr int NB = DKVH / 32 / QS, KG = 4 * QS;  // blocks of this wave; steps per group
+    static_assert(DN == DV, "halves of equal width");
+    const int b0 = qw * NB;
     f32x16 acc[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[b] = f32x16{};
-    // groups of four 16-wide steps (d_c % 128 == 0): 36 loads in flight, then 32 MFMAs
-    for (int k0 = 0; k0 < dc / 16; k0 += 4) {
-      frag_t<T> cf[4], wf[4][NB];
+    // groups of KG 16-wide steps (d_c % 128 == 0): 36 or 40 loads in flight, then 32 MFMAs
+    for (int k0 = 0; k0 < dc / 16; k0 += KG) {
+      frag_t<T> cf[KG], wf[KG][NB];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < KG; ++j) {
         cf[j] = *reinterpret_cast<const frag_t<T>*>(cr + (k0 + j) * 16);
 #pragma unroll
         for (int b = 0; b < NB; ++b)
-          wf[j][b] = *reinterpret_cast<const frag_t<T>*>(wt + ((size_t)b * (dc / 16) + k0 + j) * 512);
+          wf[j][b] = *reinterpret_cast<const frag_t<T>*>(wt + ((size_t)(b0 + b) * (dc / 16) + k0 + j) * 512);
       }
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < KG; ++j)
 #pragma unroll
         for (int b = 0; b < NB; ++b) mma(acc[b], wf[j][b], cf[j]);
     }
+    if constexpr (QS == 1) {
 #pragma unroll
-    for (int b = 0; b < NB; ++b)
+      for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        const frag_t<T> f = key_ok ? acc_to_frag<T>(acc[b], hh) : frag_t<T>{};
-        if (b < DN / 32) kf[2 * b + hh] = f;
-        else vf[2 * (b - DN / 32) + hh] = f;
+        for (int hh = 0; hh < 2; ++hh) {
+          const frag_t<T> f = key_ok ? acc_to_frag<T>(acc[b], hh) : frag_t<T>{};
+          if (b < DN / 32) kf[2 * b + hh] = f;
+          else vf[2 * (b - DN / 32) + hh] = f;
+        }
+    } else {
+      // through the last slot of the ring, which is first filled after two more barriers
+      T* const xk = &sQ[NS - 1][kw * NB * 1024 + l * 8];
+      T* const xv = &sO[NS - 1][kw * NB * 1024 + l * 8];
+      static_assert(KW * NB * 1024 <= QCH * 8 * QS && KW * NB * 1024 <= OCH * 8 * QS, "fragments fit the slot");
+      T* const mine = qw == 0 ? xk : xv;
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+          *reinterpret_cast<frag_t<T>*>(mine + (2 * b + hh) * 512) = key_ok ? acc_to_frag<T>(acc[b], hh) : frag_t<T>{};
+      lds_barrier();
+#pragma unroll
+      for (int i = 0; i < 2 * NB; ++i) {
+        kf[i] = *reinterpret_cast<const frag_t<T>*>(xk + i * 512);
+        vf[i] = *reinterpret_cast<const frag_t<T>*>(xv + i * 512);
       }
+    }
 #pragma unroll
     for (int ks = DN / 16; ks < DQK / 16; ++ks) {
       kf[ks] = *reinterpret_cast<const frag_t<T>*>(kpe + krow * DR + (ks - DN / 16) * 16 + 8 * g);

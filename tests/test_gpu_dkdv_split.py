@@ -63,6 +63,23 @@ def test_last_workgroup_without_stores(S):
         assert torch.equal(store[n], fused[n]), n
 
 
+# K/V rebuilt on chip, half of the columns in each of the two waves of the same keys: equal bit
+# for bit to K/V from memory, for contractions of one to four groups of steps
+@pytest.mark.parametrize("S,H,d_c,causal", [(1, 2, 128, True), (33, 1, 256, True), (65, 3, 384, False),
+                                            (300, 2, 128, False), (1000, 2, 384, True), (2303, 1, 512, True)])
+def test_rebuilt_kv(S, H, d_c, causal):
+    import torch
+    import paper_2607_17644_amd as L
+    w = LI.WORKLOADS["v3_train_s16384"].replace(seq_len=S, n_heads=H, d_c=d_c, causal=causal, seed=S)
+    d = dev_inputs(w, LI.make_inputs(w))
+    mat = step(w, d)
+    p = problem_for(w, kv_mode=L.KV_FUSED)
+    out, lse = L.laga_attn_fwd(p, d["q"], d["c_kv"], d["k_pe"], d["w_kv_b"])
+    fused = dict(zip(NAMES, L.laga_attn_bwd(p, d["q"], d["c_kv"], d["k_pe"], d["w_kv_b"], None, out, lse, d["dout"])))
+    for n in NAMES:
+        assert torch.equal(mat[n], fused[n]), n
+
+
 @pytest.mark.parametrize("S", [300, 2100])
 def test_heads_and_batch_beside_do_not_matter(S):
     import torch
