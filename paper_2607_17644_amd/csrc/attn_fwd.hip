@@ -727,7 +727,7 @@ __global__ __launch_bounds__(256) void frag_w_kernel(const T* __restrict__ w, T*
 // Launch grid of P.n_qblocks blocks for each of `heads`, in the order that it leaves in P.
 template <typename Params>
 dim3 order_grid(Params& P, int heads) {
-  P.order = block_order(P.n_qblocks, heads, P.causal);
+  P.order = block_order(P.n_qblocks, heads, P.causal, std::is_same<Params, FwdFusedParams>::value);
   return dim3(heads * P.n_qblocks);
 }
 
