@@ -385,7 +385,13 @@ inline BlockOrder block_order(int nblk, int heads, int causal, bool fused_fwd = 
   return {heads, group, group * nblk};
 }
 __host__ __device__ __forceinline__ void ordered_block(const BlockOrder& o, unsigned id, int& bh, int& blk) {
-  const unsigned grp = id / o.ids, j = id - grp * o.ids, h0 = grp * o.group, left = o.heads - h0;
+  unsigned j = id, h0 = 0;
+  if (id >= (unsigned)o.ids) {  // (the division is most of the cost: the first group goes without)
+    const unsigned grp = id / o.ids;
+    j = id - grp * o.ids;
+    h0 = grp * o.group;
+  }
+  const unsigned left = o.heads - h0;
   const unsigned hc = left < (unsigned)o.group ? left : o.group;
   if (hc % 8 == 0) {
     const unsigned c = hc / 8, i = j / 8;
