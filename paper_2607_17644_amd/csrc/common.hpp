@@ -362,24 +362,28 @@ __device__ __forceinline__ int xcd_remap(int id, int n) {
 // last group ends the launch so. The groups are even, of at most about kOrderMasked
 // (kOrderFull without the mask) workgroups per XCD: with fewer heads in a group the heavy
 // blocks of one head run alone at its end, with more the heads' operands leave the L2 between
-// two blocks of one head. Half of that for the fused forward, which reads a head's 256 KB of
-// W_kv_b again for every key tile.
+// two blocks of one head. The fused forward reads a head's 256 KB of W_kv_b again for every
+// key tile, so its groups stay at 8 heads per XCD, half an L2, and without the mask at what
+// the XCD's CUs run at once.
 // Measured (us; one head after the other / all heads of the XCD in one group / this). Causal:
 // forward, 128 heads x 8192 tokens 2651 / 2663 / 2504, 2 x 128 x 4096 1427 / 1512 / 1370, 64
 // x 4096 377 / 328 / 328, 2 x 16 x 5001 274 / 252 / 252; dK/dV, 128 x 8192 6243 / 6442 / 5990,
-// 64/32/64-wide 4 x 16 x 2000 122 / 108 / 107; fused forward, 128 x 4096 2063 / 2145 / 1786,
-// 128 x 2410 831 / 876 / 738. No mask: forward, 128 x 4096 1291 / 1305 / 1216; dK/dV there 2944 /
-// 3214 / 2963; 64/32/64-wide, 64 x 4096 706 / 655 / 647; fused forward, 128 x 2410 1250 / 1292 /
-// 1245. Groups of half the size, causal: forward at 64/32/64, 64 x 8192 706 -> 730; of twice
-// the size, no mask: forward 128 x 4096 1305. Whole groups and an uneven rest: dK/dV, 64 x
-// 5000 1175 -> 1236; fused forward, 128 x 2410 738 -> 842.
+// 64/32/64-wide 4 x 16 x 2000 122 / 108 / 107; fused forward, 128 x 4096 2063 / 2145 / 1815, 128
+// x 2410 831 / 876 / 743, 2 x 128 x 745 248 / 294 / 225, 64 x 4096 1090 / 886 / 886. No mask:
+// forward, 128 x 4096 1291 / 1305 / 1216; dK/dV there 2944 / 3214 / 2963; 64/32/64-wide, 64 x
+// 4096 706 / 655 / 647; fused forward, 2 x 128 x 1569 1179 / 1276 / 1175. Groups of half the
+// size, causal: forward at 64/32/64, 64 x 8192 706 -> 730; of twice the size, no mask: forward
+// 128 x 4096 1305. Whole groups and an uneven rest: dK/dV, 64 x 5000 1175 -> 1236.
 constexpr int kOrderMasked = 256, kOrderFull = 128;
 struct BlockOrder {
   int heads, group, ids;  // B * H; heads of a group (a multiple of 8 unless it is the only one); its workgroups
 };
+constexpr int kOrderFusedMasked = 128, kOrderFusedFull = 32, kOrderFusedHeads = 8;  // the fused forward; heads per XCD
 inline BlockOrder block_order(int nblk, int heads, int causal, bool fused_fwd = false) {
-  const int size = (causal ? kOrderMasked : kOrderFull) / (fused_fwd ? 2 : 1);
-  const int per_xcd = (heads + 7) / 8, most = (size + nblk - 1) / nblk;
+  const int size = fused_fwd ? (causal ? kOrderFusedMasked : kOrderFusedFull) : causal ? kOrderMasked : kOrderFull;
+  int most = (size + nblk - 1) / nblk;
+  if (fused_fwd && most > kOrderFusedHeads) most = kOrderFusedHeads;
+  const int per_xcd = (heads + 7) / 8;
   const int groups = (per_xcd + most - 1) / most, even = 8 * ((per_xcd + groups - 1) / groups);
   const int group = heads < even ? heads : even;
   return {heads, group, group * nblk};

@@ -19,12 +19,14 @@ int main() {
       for (int heads : {1, 2, 3, 4, 5, 7, 8, 9, 12, 15, 16, 17, 20, 24, 32, 60, 64, 100, 124, 128, 256, 520, 4096}) {
         const int causal = mode & 1, fused = mode >> 1;
         const laga::BlockOrder o = laga::block_order(nblk, heads, causal, fused);
-        const int target = (causal ? laga::kOrderMasked : laga::kOrderFull) / (fused ? 2 : 1);
+        const int target = fused ? (causal ? laga::kOrderFusedMasked : laga::kOrderFusedFull)
+                                 : causal ? laga::kOrderMasked : laga::kOrderFull;
         if (o.heads != heads || (o.group != heads && o.group % 8) || o.group > heads || o.ids != o.group * nblk)
           fail("group", nblk, heads, causal);
         if (o.ids >= 8 * (target + nblk)) fail("a group too large", nblk, heads, causal);
         // even groups, as few as the size allows
-        const int most = (target + nblk - 1) / nblk, groups = (heads + o.group - 1) / o.group;
+        const int wide = (target + nblk - 1) / nblk, groups = (heads + o.group - 1) / o.group;
+        const int most = fused && wide > laga::kOrderFusedHeads ? laga::kOrderFusedHeads : wide;
         if (groups > ((heads + 7) / 8 + most - 1) / most) fail("too many groups", nblk, heads, causal);
         if (groups > 1 && heads - (groups - 1) * o.group + 8 * groups <= o.group) fail("an uneven rest", nblk, heads, causal);
         std::vector<int> seen((size_t)nblk * heads, 0), xcd(heads, -1);
