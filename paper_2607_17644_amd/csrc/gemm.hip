@@ -915,15 +915,6 @@ hipError_t launch_gemm_nt(const T* a, const T* w, T* c, int M, int N, int K, hip
   return hipGetLastError();
 }
 
-int gemm_tn_splits(int M, int N, int K, int esize) {
-  const bool large = esize == 2 && K % kGK == 0;
-  const int tiles = large ? grid_tiles(M, N, 256, 256) : grid_tiles(M, N, 128, 128);
-  const int want = large ? kCUs : 2 * kCUs;
-  int n = (want + tiles - 1) / tiles;
-  const int max_split = (K + 511) / 512;
-  return n < 1 ? 1 : (n > max_split ? max_split : n);
-}
-
 template <typename T>
 hipError_t launch_gemm_tn(const T* a, const T* b, float* c, float* partial, int M, int N, int K, int nsplit,
                           hipStream_t st) {

@@ -120,6 +120,19 @@ inline DcRanges dc_ranges(int splits, int K, int step) {
   return {chunk, (K + chunk - 1) / chunk};
 }
 
+// Splits of gemm_tn's contraction of K indices for an M x N output (dw_o): enough for two 128 x
+// 128 workgroups per CU and no more than for one 256 x 256, each split at least 512 indices; a
+// function of the shape only, and never more than were ever reported as workspace for it.
+// Measured (us, the whole backward of W_o, splits in brackets; the second count alone, which
+// used to decide where K is a multiple of 32 / this: the sum of the partials costs more than
+// the workgroups gain): T 2048, F 2048, D 7168 173 (2) / 132 (1); T 1024, F 2048, D 4096 79 (2) / 59
+// (1); T 2048, F 2048, D 2048 65 (4) / 57 (2).
+inline int gemm_tn_splits(int M, int N, int K) {
+  const int small = grid_tiles(M, N, 128, 128), large = grid_tiles(M, N, 256, 256);
+  const int n = std::min((2 * kCUs + small - 1) / small, (kCUs + large - 1) / large);
+  return std::max(1, std::min(n, (K + 511) / 512));
+}
+
 // Workspace of the split partials of dc_kv (its contraction, over the shard's heads x 256, is
 // split so that the launch has enough workgroups; dc_kv sums over heads, so no bit-identity
 // across head shards is asked of it) and of dW.

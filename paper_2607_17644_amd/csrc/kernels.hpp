@@ -46,9 +46,6 @@ hipError_t launch_gemm_nt(const T* a, const T* w, T* c, int M, int N, int K, hip
 template <typename T>
 hipError_t launch_gemm_tn(const T* a, const T* b, float* c, float* partial, int M, int N, int K, int nsplit,
                           hipStream_t st);
-// contraction splits gemm_tn is given for an M x N output over K (element size esize):
-// enough workgroups for the GPU, each split at least 512 indices; a function of the shape only
-int gemm_tn_splits(int M, int N, int K, int esize);
 
 struct AttnFwdArgs {
   const void* q;      // [B,S,H,DN+DR]

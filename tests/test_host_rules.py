@@ -11,7 +11,7 @@ from paper_2607_17644_amd import build as B
 HOST = os.path.join(os.path.dirname(os.path.abspath(__file__)), "host")
 
 
-@pytest.mark.parametrize("name", ["dkdv_split_waits", "gemm_ranges", "block_order", "ring_tiles"])
+@pytest.mark.parametrize("name", ["dkdv_split_waits", "gemm_ranges", "block_order", "ring_tiles", "out_proj_splits"])
 def test_rule(name, tmp_path):
     exe = str(tmp_path / name)
     r = subprocess.run([B.HIPCC, "-x", "hip", "--offload-host-only", "-O1", "-std=c++17", "-I",
