@@ -149,8 +149,11 @@ laga_status_t validate_out_proj(const laga_out_proj_t* p, OutDims* d) {
   d->T = (int)p->tokens; d->F = (int)F; d->D = (int)p->d_model;
   return LAGA_OK;
 }
-size_t out_proj_ws_bytes(const OutDims& d) {
-  const int n = gemm_tn_splits(d.F, d.D, d.T);
+int out_proj_splits(const laga_out_proj_t* p, const OutDims& d) {
+  return gemm_tn_splits(d.F, d.D, d.T, p->dtype == LAGA_DTYPE_BF16 ? 2 : 4);
+}
+size_t out_proj_ws_bytes(const laga_out_proj_t* p, const OutDims& d) {
+  const int n = out_proj_splits(p, d);
   return n > 1 ? round_up(sizeof(float) * (size_t)n * d.F * d.D) : 0;
 }
 
@@ -269,7 +272,7 @@ laga_status_t laga_prologue_bwd(const laga_problem_t* p, const laga_prologue_t* 
 size_t laga_out_proj_workspace_bytes(const laga_out_proj_t* p) {
   OutDims d;
   if (validate_out_proj(p, &d) != LAGA_OK) return 0;
-  return out_proj_ws_bytes(d);
+  return out_proj_ws_bytes(p, d);
 }
 
 laga_status_t laga_out_proj_fwd(const laga_out_proj_t* p, const void* out, const void* w_o, void* y, void* stream) {
@@ -293,11 +296,11 @@ laga_status_t laga_out_proj_bwd(const laga_out_proj_t* p, const void* out, const
   if (!out || !w_o || !dy || !d_out || !dw_o) return LAGA_ERR_NULL;
   if (misaligned(out) || misaligned(w_o) || misaligned(dy) || misaligned(d_out) || misaligned(dw_o))
     return LAGA_ERR_ALIGN;
-  const size_t need = out_proj_ws_bytes(d);
+  const size_t need = out_proj_ws_bytes(p, d);
   if (need > 0 && (!workspace || workspace_bytes < need)) return LAGA_ERR_WORKSPACE;
   if (need > 0 && misaligned(workspace)) return LAGA_ERR_ALIGN;
   hipStream_t st = (hipStream_t)stream;
-  const int ns = gemm_tn_splits(d.F, d.D, d.T);
+  const int ns = out_proj_splits(p, d);
   hipError_t e;
   if (p->dtype == LAGA_DTYPE_BF16) {
     // d_out[T][F] = dy[T][D] @ w_o^T (w_o stored [F][D]: k-contiguous); dw_o[F][D] = out^T @ dy

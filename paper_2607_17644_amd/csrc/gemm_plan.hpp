@@ -120,16 +120,18 @@ inline DcRanges dc_ranges(int splits, int K, int step) {
   return {chunk, (K + chunk - 1) / chunk};
 }
 
-// Splits of gemm_tn's contraction of K indices for an M x N output (dw_o): enough for two 128 x
-// 128 workgroups per CU and no more than for one 256 x 256, each split at least 512 indices; a
-// function of the shape only, and never more than were ever reported as workspace for it.
-// Measured (us, the whole backward of W_o, splits in brackets; the second count alone, which
-// used to decide where K is a multiple of 32 / this: the sum of the partials costs more than
-// the workgroups gain): T 2048, F 2048, D 7168 173 (2) / 132 (1); T 1024, F 2048, D 4096 79 (2) / 59
-// (1); T 2048, F 2048, D 2048 65 (4) / 57 (2).
-inline int gemm_tn_splits(int M, int N, int K) {
+// Splits of gemm_tn's contraction of K indices for an M x N output (dw_o), each at least 512
+// indices; a function of the shape only, and never more than were ever reported as workspace
+// for it. fp32: enough for two 128 x 128 workgroups per CU. bf16: that many, and no more than
+// for one 256 x 256 workgroup per CU. The latter alone used to decide where K is a multiple of
+// 32, and the sum of its partials costs more than the workgroups gain (us, the whole backward
+// of W_o, splits in brackets): T 2048, F 2048, D 7168 173 (2) / 132 (1); T 1024, F 2048, D 4096 79
+// (2) / 59 (1); T 2048, F 2048, D 2048 65 (4) / 57 (2). From 4096 indices on it costs nothing (T
+// 16384, F 2048, D 4096 486 (2) / 496 (1)) and stays as reported before, by K % 32.
+inline int gemm_tn_splits(int M, int N, int K, int esize) {
   const int small = grid_tiles(M, N, 128, 128), large = grid_tiles(M, N, 256, 256);
-  const int n = std::min((2 * kCUs + small - 1) / small, (kCUs + large - 1) / large);
+  const int ns = (2 * kCUs + small - 1) / small, nl = (kCUs + large - 1) / large;
+  const int n = esize == 4 ? ns : K < 4096 ? std::min(ns, nl) : K % kGK == 0 ? nl : ns;
   return std::max(1, std::min(n, (K + 511) / 512));
 }
 
