@@ -160,3 +160,28 @@ def test_tail_rows_do_not_leak():
     ref = out.reshape(T, 64).double().t() @ dy.double()
     assert torch.equal(torch.isfinite(dw), torch.isfinite(ref))
     assert torch.equal(dw[0].isinf(), ref[0].isinf()) and bool(dw[0].isinf().all())
+
+
+# kv and dW columns of a head, whatever the number of heads: 2048 tokens take small tiles (4
+# heads), middle (16), large (18) and the persistent kernel (32); 2200 the last of them ragged;
+# 300 share dc's and dW's launch at 16 heads and not at 64; 1100 split dW's tokens
+@pytest.mark.parametrize("T,heads", [(2048, (4, 16, 18, 32)), (2200, (4, 16, 32)), (300, (1, 16, 64)),
+                                     (1100, (2, 16, 40))])
+def test_columns_do_not_depend_on_the_heads(T, heads):
+    import torch
+    import paper_2607_17644_amd as L
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    H = max(heads)
+    c, kpe, q, dout = randn(gen, 1, T, 512), randn(gen, 1, T, 64), randn(gen, 1, T, H, 192), randn(gen, 1, T, H, 128)
+    w = (randn(gen, 512, H * 256).float() * 512 ** -0.5).to(torch.bfloat16)
+    res = {}
+    for h in heads:
+        p = L.Problem(1, T, h, 512, 128, 64, 128, 192 ** -0.5, dq_mode=L.DQ_RECOMPUTE)
+        qh, dh, wh = q[:, :, :h].contiguous(), dout[:, :, :h].contiguous(), w[:, :h * 256].contiguous()
+        kv = L.laga_reconstruct_kv(p, c, wh)
+        out, lse = L.laga_attn_fwd(p, qh, c, kpe, wh, kv)
+        res[h] = kv, L.laga_attn_bwd(p, qh, c, kpe, wh, kv, out, lse, dh)[3]
+    for h in heads:
+        n = min(heads)
+        assert torch.equal(res[h][0][:, :, :n], res[n][0]), h
+        assert torch.equal(res[h][1][:, :n * 256], res[n][1]), h
