@@ -894,11 +894,11 @@ hipError_t launch_bwd_dq(bwd::BwdParams P, int B, hipStream_t st) {
     P.n_blocks = (P.S + 32 * RW - 1) / (32 * RW);
     const dim3 grid = order_grid(P, B);
     dq_rec_kernel<DN, DR, DV, RW><<<grid, 64 * RW, 0, st>>>(P);
-    return hipGetLastError();
+  } else {
+    P.n_blocks = (P.S + 63) / 64;
+    const dim3 grid = order_grid(P, B);
+    dq_kernel<T, DN, DR, DV><<<grid, 256, 0, st>>>(P);
   }
-  P.n_blocks = (P.S + 63) / 64;
-  const dim3 grid = order_grid(P, B);
-  dq_kernel<T, DN, DR, DV><<<grid, 256, 0, st>>>(P);
   return hipGetLastError();
 }
 

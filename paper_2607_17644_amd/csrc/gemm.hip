@@ -16,11 +16,13 @@
 // head) runs large problems on a persistent variant that spreads each tile's stores over
 // the next tile's MFMAs (gemm_stream_kernel). fp32: the register-staged gemm_kernel.
 //
-// Per output element the contraction runs over K in ascending 16-wide steps
-// (one MFMA each) with fp32 accumulation; tile shapes and the dW token split do
-// not depend on N, so a column of the output is bit-identical whatever N (the
-// number of heads) is. (dc_kv's contraction runs over the heads and may be split
-// into partials summed in a fixed order.)
+// Per output element the contraction runs over K in ascending 16-wide steps (one MFMA each;
+// hi before lo where an operand is a pair) with fp32 accumulation. Tile shape, the persistent
+// kernel and the shared launch of dc and dW are chosen by sizes that include N, the number of
+// heads' columns: a column of kv or dW is bit-identical whatever N is only because every one
+// of them accumulates an output in this same order, and because dW's token split does not
+// depend on N. (dc_kv's contraction runs over the heads and may be split into partials summed
+// in a fixed order.)
 // direct global->LDS copies issued as inline assembly (exact LDS-read waits; the
 // ring orders the copies with explicit waits and barriers)
 #define LAGA_LDS_DMA_ASM 1
@@ -44,12 +46,14 @@ __device__ __forceinline__ int xcd_remap_any(int id, int n) {
   return x * (n / 8) + min(x, n % 8) + id / 8;
 }
 
-template <typename T, bool KSTRIDED, int ROWS, int BK>
+// One operand's tile of the fp32 kernel, staged through registers.
+template <bool KSTRIDED, int ROWS, int BK>
 struct OperandTile {
+  using T = float;
   static constexpr int E = Elems16<T>::n;                      // elements per 16-byte chunk
   // k-contiguous rows: +8 elements keeps 16-byte fragment reads conflict-free and
   // fp32 rows 32-byte aligned; k-strided rows: +32 bytes for the transposing reads.
-  static constexpr int PITCH = KSTRIDED ? ROWS + 32 / (int)sizeof(T) : BK + 8;
+  static constexpr int PITCH = KSTRIDED ? ROWS + 8 : BK + 8;
   static constexpr int LDS_ELEMS = KSTRIDED ? BK * PITCH : ROWS * PITCH;
   static constexpr int CHUNKS = ROWS * BK / E;
   static constexpr int PER_THREAD = CHUNKS / kThreads;
@@ -114,12 +118,13 @@ __device__ __forceinline__ void store4<bf16>(bf16* p, float a, float b, float c,
 // two / four steps ahead): 256 tokens, d_c 64, N 256: dc and dW 10.9 / 9.3 / 8.6 each; 2048
 // tokens, d_c 512, N 4096: dc, dW and the reconstruct 272 / 264 / 249 together (four steps: 104
 // TFLOP/s; the rest is the step's own chain, LDS store, barrier, LDS read, MFMA).
-template <typename T, typename TO, bool A_KS, bool B_KS, int BM, int BN, int BK>
+template <bool A_KS, bool B_KS, int BM, int BN, int BK>
 __global__ __launch_bounds__(kThreads) void gemm_kernel(
-    const T* __restrict__ A, const T* __restrict__ B, TO* __restrict__ C,
+    const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C,
     int M, int N, int K, int lda, int ldb, int ldc, int k_chunk, long long split_stride) {
-  using TA = OperandTile<T, A_KS, BM, BK>;
-  using TB = OperandTile<T, B_KS, BN, BK>;
+  using T = float;
+  using TA = OperandTile<A_KS, BM, BK>;
+  using TB = OperandTile<B_KS, BN, BK>;
   constexpr int WM = BM / 64, WN = BN / 64;  // 32x32 blocks per wave along m and n
   constexpr int kAhead = 4;
   __shared__ __attribute__((aligned(16))) T sA[2][TA::LDS_ELEMS];
@@ -182,7 +187,7 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(
     }
   }
 
-  TO* Cz = C + blockIdx.z * split_stride;
+  float* Cz = C + blockIdx.z * split_stride;
 #pragma unroll
   for (int j = 0; j < WN; ++j)
 #pragma unroll
@@ -193,7 +198,7 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(
       for (int rr = 0; rr < 4; ++rr) {
         const int n = n0 + (wn * WN + j) * 32 + rr * 8 + g * 4;
         if (n < N)
-          store4<TO>(Cz + (size_t)m * ldc + n, acc[j][i][4 * rr], acc[j][i][4 * rr + 1],
+          store4<float>(Cz + (size_t)m * ldc + n, acc[j][i][4 * rr], acc[j][i][4 * rr + 1],
                      acc[j][i][4 * rr + 2], acc[j][i][4 * rr + 3]);
       }
     }
@@ -311,11 +316,11 @@ struct GRead {
 };
 
 // C (+ blockIdx.z * split_stride) [M][N] = A[M][k range] B[k range][N], bf16 operands,
-// fp32 accumulation, on NWV waves in a WGM x (NWV / WGM) grid of wave tiles. SPLIT as in
-// gemm_kernel (1: A + X2, 2: B + X2; hi before lo per k-step). M and N are arbitrary for
-// k-contiguous operands and at least 8 for k-strided ones (rows or columns past the end
-// are copied from the last ones and not stored). The contraction of a split may end
-// anywhere if both operands are k-strided, else at a multiple of 16: the last stage then
+// fp32 accumulation, on NWV waves in a WGM x (NWV / WGM) grid of wave tiles. SPLIT: an
+// operand is the sum of two bf16 tensors (1: A + X2, 2: B + X2; hi before lo per k-step). M and
+// N are arbitrary for k-contiguous operands and at least 8 for k-strided ones (rows or columns
+// past the end are copied from the last ones and not stored). The contraction of a split may
+// end anywhere if both operands are k-strided, else at a multiple of 16: the last stage then
 // copies in-bounds rows (k-strided) or chunks (k-contiguous) in the place of the missing
 // ones, k-strided rows past the end are zeroed in LDS before they are read, and a second
 // 16-wide step with nothing in it is left out.
@@ -526,8 +531,10 @@ constexpr int kStreamStoreStages = 16;  // stages over which a tile's stores are
 constexpr int kStreamMaxK = 1024;       // longest contraction it is launched for
 
 
-// RAGGED: the last row tile is partial (a variant of its own: the row limits in the whole-tile
-// one cost it 8 % at 16384 rows).
+// RAGGED: the last row tile is partial (a variant of its own). It spills 69 registers (the
+// whole-tile one 29, outside its stages): a store's 64-bit row address is reloaded from scratch
+// in each of the sixteen store stages, and that wait drains the copies in flight. Measured (us,
+// 16 heads, d_c 512): 16383 rows 82, 16384 75; 10002 rows 61, 9984 58.
 template <int BM, int BN, bool A_KS, bool B_KS, bool RAGGED>
 __global__ __launch_bounds__(512, 1) void gemm_stream_kernel(const bf16* __restrict__ A, const bf16* __restrict__ B,
                                                              bf16* __restrict__ C, int M, int N, int K, int lda,
@@ -738,8 +745,8 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const float* __restri
   reinterpret_cast<f32x4*>(dst)[i] = s;
 }
 
-template <typename T> struct GemmCfg;
-template <> struct GemmCfg<float> { static constexpr int BM = 64, BN = 64, BK = kFp32GK; };
+// fp32 tile of gemm_kernel
+struct GemmCfg { static constexpr int BM = 64, BN = 64, BK = kFp32GK; };
 
 // The backward's last launch: dc and dW from their split partials (ascending splits) and
 // dk_pe[t, :] = sum over heads (ascending) of the per-head parts, 4 values per thread. One
@@ -821,8 +828,8 @@ hipError_t launch_reconstruct(const T* c, const T* w, T* kv, int M, int N, int K
                                                   /*k_chunk=*/K, 1, st);
     }
   } else {
-    using G = GemmCfg<T>;
-    gemm_kernel<T, T, false, true, G::BM, G::BN, G::BK><<<grid_tiles(M, N, G::BM, G::BN), kThreads, 0, st>>>(
+    using G = GemmCfg;
+    gemm_kernel<false, true, G::BM, G::BN, G::BK><<<grid_tiles(M, N, G::BM, G::BN), kThreads, 0, st>>>(
         c, w, kv, M, N, K, /*lda=*/K, /*ldb=*/N, /*ldc=*/N, /*k_chunk=*/K, 0);
   }
   return hipGetLastError();
@@ -873,20 +880,20 @@ hipError_t launch_finish(const FinishParams& f, hipStream_t st) {
         launch_ring<256, 256, true, true, 2, float>(c, dkv, lo, dw, N, K, M, N, K, K, split, nw, st);
     }
   } else {
-    using G = GemmCfg<T>;
+    using G = GemmCfg;
     // dc's contraction in the plan's splits here too: one 64 x 64 tile per CU leaves the CUs
     // waiting on its loads (2048 tokens, 16 heads: 141 us in one range, 94 in four)
     const DcRanges r = dc_ranges(plan.splits, K, G::BK);
     const int k_chunk = r.chunk;
     nz = r.n;
-    gemm_kernel<T, float, false, false, G::BM, G::BN, G::BK><<<dim3(grid_tiles(M, N, G::BM, G::BN), 1, nz), kThreads, 0,
+    gemm_kernel<false, false, G::BM, G::BN, G::BK><<<dim3(grid_tiles(M, N, G::BM, G::BN), 1, nz), kThreads, 0,
                                                                st>>>(dkv, w, nz == 1 ? f.dc : dc_part, M, N, K, K, K, N,
                                                                      k_chunk, sdc);
     if (!plan.pair && nz > 1) {
       split_reduce_kernel<<<(unsigned)((sdc / 4 + 255) / 256), 256, 0, st>>>(dc_part, f.dc, sdc / 4, nz, sdc);
       nz = 1;
     }
-    gemm_kernel<T, float, true, true, G::BM, G::BN, G::BK><<<dim3(grid_tiles(N, K, G::BM, G::BN), 1, nw), kThreads, 0,
+    gemm_kernel<true, true, G::BM, G::BN, G::BK><<<dim3(grid_tiles(N, K, G::BM, G::BN), 1, nw), kThreads, 0,
                                                              st>>>(c, dkv, nw == 1 ? f.dw : dw_part, N, K, M, N, K, K,
                                                                    split, sdw);
   }
@@ -908,8 +915,8 @@ hipError_t launch_gemm_nt(const T* a, const T* w, T* c, int M, int N, int K, hip
   if constexpr (sizeof(T) == 2) {
     launch_ring<256, 256, false, false, 0, bf16>(a, w, nullptr, c, M, N, K, K, K, N, K, 1, st);
   } else {
-    using G = GemmCfg<T>;
-    gemm_kernel<T, T, false, false, G::BM, G::BN, G::BK><<<grid_tiles(M, N, G::BM, G::BN), kThreads, 0, st>>>(
+    using G = GemmCfg;
+    gemm_kernel<false, false, G::BM, G::BN, G::BK><<<grid_tiles(M, N, G::BM, G::BN), kThreads, 0, st>>>(
         a, w, c, M, N, K, K, K, N, K, 0);
   }
   return hipGetLastError();
@@ -926,8 +933,8 @@ hipError_t launch_gemm_tn(const T* a, const T* b, float* c, float* partial, int 
   if constexpr (sizeof(T) == 2) {
     launch_ring<256, 256, true, true, 0, float>(a, b, nullptr, target, M, N, K, M, N, N, split, nz, st);
   } else {
-    using G = GemmCfg<T>;
-    gemm_kernel<T, float, true, true, G::BM, G::BN, G::BK><<<dim3(grid_tiles(M, N, G::BM, G::BN), 1, nz), kThreads, 0,
+    using G = GemmCfg;
+    gemm_kernel<true, true, G::BM, G::BN, G::BK><<<dim3(grid_tiles(M, N, G::BM, G::BN), 1, nz), kThreads, 0,
                                                              st>>>(a, b, target, M, N, K, M, N, N, split,
                                                                    (long long)M * N);
   }
